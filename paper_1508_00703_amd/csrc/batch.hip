@@ -35,6 +35,20 @@ constexpr int kG = 8;                     // examples a wave loads together in p
 constexpr int kH = 8;                     // union features a thread takes in phase 2
 constexpr int64_t kCap = kBB * kH;        // entries of a batch staged in LDS (8192)
 
+// the sync-free epoch example by example (k_batch_flow): entries and examples of
+// a batch, entries on features with several
+constexpr int kFlowCap = 16384;
+constexpr int kFlowB = 256;
+constexpr int kFlowOcc = 4096;
+constexpr int kFlowMany = kFlowCap;  // codes from here on: features with several entries
+// the block's waves: workers, which run up to kFlowG examples each, and
+// pollers, which wait for up to kFlowSlots words per lane
+constexpr int kFlowWorkers = 13;
+constexpr int kFlowPollers = kBWaves - kFlowWorkers;
+constexpr int kFlowG = 8;
+constexpr int kFlowSlots = 16;
+constexpr int kFlowList = kFlowPollers * kWave * kFlowSlots;
+
 // LDS of a batch block: steps by example; for staged batches the weights read
 // in phase 1 by entry, and per occurrence its example (relative to the
 // batch) and value
@@ -397,41 +411,6 @@ __global__ void k_bw_out(const unsigned long long *__restrict__ bw, float *__res
         w[f] = word_value(bw[f]);
 }
 
-// Polls the words f[h] of the slots not yet ready until each carries tag[h];
-// every round reloads all of them at once, so a wave confirms several
-// arrivals in one round trip.  False on timeout or abort.
-template <int H>
-__device__ __forceinline__ bool bw_wait_slots(unsigned long long *base, const int32_t *f,
-                                              const int32_t *tag, bool *ready,
-                                              unsigned long long *v, Ctrl *ctrl,
-                                              int64_t timeout) {
-    int64_t t0 = 0;
-    for (int round = 0;; ++round) {
-        bool all = true;
-#pragma unroll
-        for (int h = 0; h < H; ++h) all = all && ready[h];
-        if (__ballot(!all) == 0ull) return true;
-        if (round == 0) {
-            t0 = now_ticks();
-        } else {
-            if (aborted(ctrl)) return false;
-            if (now_ticks() - t0 > timeout) {
-                record_error(ctrl, DERR_WAIT_TIMEOUT);
-                return false;
-            }
-        }
-        word_backoff(round);
-        __asm__ __volatile__("" ::: "memory");  // the loads below are issued again
-#pragma unroll
-        for (int h = 0; h < H; ++h) {
-            if (!ready[h]) {
-                v[h] = word_get(base, f[h]);
-                ready[h] = (int)(unsigned)(v[h] >> 32) == tag[h];
-            }
-        }
-    }
-}
-
 // A value every thread of the block reads from the same LDS word after a
 // barrier, made wave-uniform for the compiler: the ticket loop's exits and
 // the block barriers inside it then compile to scalar branches, so every
@@ -449,8 +428,8 @@ __device__ __forceinline__ int64_t block_uniform64(int64_t v) {
 struct SfShared {
     float s[kMaxBatch];
     float uw[kCap];
-    int32_t eu[kCap];
-    int32_t oi[kCap];
+    int32_t eu[kCap];   // fast_batch: union feature | occurrence position << 16
+    int32_t oi[kCap];   // fast_batch: the occurrences' steps
     float ox[kCap];
     int64_t ticket;
     int ok;
@@ -529,110 +508,173 @@ __device__ bool general_batch(const BatchOp<LOSS, VAL> &op, const int32_t *uprev
 
 // A batch of at most kBWaves * kG examples and kCap entries.  Everything
 // that does not depend on other batches comes first -- each wave's example
-// bounds, labels and values in registers, every occurrence's example, value
-// and union feature in LDS, each thread's union features in registers --
-// then the words are read once and only those not yet written by their
-// previous writer are polled; after that both phases read LDS only.
+// bounds, labels and values in registers, every entry's union feature and
+// occurrence position and every occurrence's value in LDS, each thread's union
+// features in registers -- then the words are read once and only those not
+// yet written by their previous writer are polled; after that both phases
+// run from LDS.  Sixteen waves share the unit's issue slots, and what lies
+// between the last word's arrival and the publish is bound by them: every
+// loop over a wave's examples or union features ends, by a scalar branch,
+// with the ones the batch has (issuing all kG and kH of them, masked, took
+// 35.1 ms where this takes 25.5: 5,000 batches of 100 examples of 50 Zipf-1.2
+// features, 7.0 -> 5.1 us a batch).
 template <int LOSS, bool VAL>
 __device__ bool fast_batch(const BatchOp<LOSS, VAL> &op, const int32_t *uprev,
                            unsigned long long *bw, SfShared &Sh, int64_t b, int64_t nb,
                            int64_t i0, int64_t i1, int64_t pb, int64_t pe, int64_t ub,
                            int64_t ue, Ctrl *ctrl, int64_t timeout) {
     const int lane = lane_id();
-    const int wave = (int)(threadIdx.x >> 6);
-    // this wave's examples i0 + wave + kBWaves * j, j < kG
+    const int wave = block_uniform((int)(threadIdx.x >> 6));
+    const int nE = (int)(pe - pb), nU = (int)(ue - ub);
+    // this wave's examples i0 + wave + kBWaves * j, j < jn; this lane's union
+    // features u0 + kBB * h, h < hn (the last may lie past nU)
+    const int jn = block_uniform(max((int)(i1 - i0) - wave + kBWaves - 1, 0) / kBWaves);
+    const int hn = block_uniform(max(nU - wave * kWave + kBB - 1, 0) / kBB);
+    const int u0 = wave * kWave + lane;
     const int64_t my_i = i0 + wave + (int64_t)kBWaves * lane;
     const bool has = lane < kG && my_i < i1;
     const int64_t rb = op.row_ptr[has ? my_i : i0];
-    const int64_t re = has ? op.row_ptr[my_i + 1] : rb;
+    const int num = has ? (int)(op.row_ptr[my_i + 1] - rb) : 0;
+    const int rel = (int)(rb - pb);
     const float yv = op.y[has ? my_i : i0];
-    int32_t p[kG], m[kG];  // first entry relative to pb, entry count
-#pragma unroll
-    for (int j = 0; j < kG; ++j) {
-        const int64_t r0 = readlane64(rb, j);
-        p[j] = (int32_t)(r0 - pb);
-        m[j] = (int32_t)(readlane64(re, j) - r0);
+    // example j's first entry relative to pb, and its entry count
+    auto first = [&](int j) { return __builtin_amdgcn_readlane(rel, j); };
+    auto count = [&](int j) { return __builtin_amdgcn_readlane(num, j); };
+    for (int q = threadIdx.x; q < nE; q += kBB) {
+        const int32_t pq = op.occ[pb + q];
+        if (VAL) Sh.ox[q] = op.val[pq];
+        Sh.eu[pq - pb] = (op.occ_u[pb + q] - (int32_t)ub) | q << 16;
     }
-    float x[2 * kG];
-#pragma unroll
-    for (int t = 0; t < 2 * kG; ++t) {
-        x[t] = 1.0f;
-        if (VAL && pe > pb)
-            x[t] = op.val[min(max(pb + p[t >> 1] + (t & 1) * kWave + lane, pb), pe - 1)];
-    }
-    for (int64_t q = pb + threadIdx.x; q < pe; q += kBB) {
-        const int32_t pq = op.occ[q];
-        Sh.oi[q - pb] = op.occ_row[q] - (int32_t)i0;
-        if (VAL) Sh.ox[q - pb] = op.val[pq];
-        Sh.eu[pq - pb] = op.occ_u[q] - (int32_t)ub;
-    }
-    int32_t f[kH], tag[kH], q0[kH], q1[kH];
-    bool urgent[kH];  // the next batch writes this feature too: publish it first
-    // union entries of the batches up to the next one end at soon_end
+    // union features: feature, previous union entry, occurrences q0 | q1 << 16,
+    // and whether the next batch writes the feature too (publish those first;
+    // union entries of the batches up to the next one end at soon_end)
+    int32_t f[kH], tag[kH], qq[kH];
+    float w[kH];
+    unsigned urgent = 0, pend = 0;
     const int64_t soon_end = op.unext ? op.bptr[min(b + 2, nb)] : 0;
 #pragma unroll
     for (int h = 0; h < kH; ++h) {
-        const int64_t u = ub + threadIdx.x + (int64_t)kBB * h;
-        const bool live = u < ue;
-        f[h] = live ? op.ucol[u] : 0;
-        tag[h] = live ? uprev[u] : -1;
-        q0[h] = live ? (int32_t)(op.uptr[u] - pb) : 0;
-        q1[h] = live ? (int32_t)(op.uptr[u + 1] - pb) : 0;
-        const int32_t nx = (live && op.unext) ? op.unext[u] : -1;
-        urgent[h] = nx >= 0 && nx < soon_end;
+        f[h] = tag[h] = qq[h] = 0;
+        w[h] = 0.0f;
+        if (h >= hn) continue;
+        const int u = u0 + kBB * h;
+        if (u < nU) {
+            f[h] = op.ucol[ub + u];
+            tag[h] = uprev[ub + u];
+            qq[h] = (int)(op.uptr[ub + u] - pb) | (int)(op.uptr[ub + u + 1] - pb) << 16;
+            const int32_t nx = op.unext ? op.unext[ub + u] : -1;
+            urgent |= nx >= 0 && nx < soon_end ? 1u << h : 0u;
+            pend |= 1u << h;
+        }
     }
-    // reads: every word once, then a wait for those not yet written
-    unsigned long long v[kH];
-    bool ready[kH];
+    float x[VAL ? 2 * kG : 1];
+    if constexpr (VAL) {
+#pragma unroll
+        for (int t = 0; t < 2 * kG; ++t) {
+            const int k = (t & 1) * kWave + lane;
+            x[t] = k < count(t >> 1) ? op.val[pb + first(t >> 1) + k] : 0.0f;
+        }
+    }
+    __syncthreads();
+    int32_t at[2 * kG];  // each entry's union feature | occurrence position << 16
+#pragma unroll
+    for (int t = 0; t < 2 * kG; ++t) {
+        const int k = (t & 1) * kWave + lane;
+        at[t] = k < count(t >> 1) ? Sh.eu[first(t >> 1) + k] : 0;
+    }
+    // reads: every word once, then those not yet written until they are
+    int64_t t0 = 0;
+    bool ok = true;
+    for (int round = 0;; ++round) {
+        unsigned long long v[kH];
+#pragma unroll
+        for (int h = 0; h < kH; ++h) {
+            if (h >= hn) break;
+            if (pend >> h & 1) v[h] = word_get(bw, f[h]);
+        }
+#pragma unroll
+        for (int h = 0; h < kH; ++h) {
+            if (h >= hn) break;
+            if ((pend >> h & 1) && word_tag(v[h]) == tag[h]) {
+                w[h] = word_value(v[h]);
+                pend &= ~(1u << h);
+            }
+        }
+        if (__ballot(pend != 0) == 0ull) break;
+        // the abort flag is a device-scope load: not on the path of every poll
+        if (round == 0) {
+            t0 = now_ticks();
+        } else if ((round & 31) == 0) {
+            ok = !aborted(ctrl);
+            if (ok && now_ticks() - t0 > timeout) {
+                record_error(ctrl, DERR_WAIT_TIMEOUT);
+                ok = false;
+            }
+            if (!ok) break;
+        }
+        word_backoff_short(round);
+        __asm__ __volatile__("" ::: "memory");  // the next round loads again
+    }
 #pragma unroll
     for (int h = 0; h < kH; ++h) {
-        const bool live = ub + threadIdx.x + (int64_t)kBB * h < ue;
-        v[h] = live ? word_get(bw, f[h]) : 0ull;
-        ready[h] = !live || (int)(unsigned)(v[h] >> 32) == tag[h];
+        if (h >= hn) break;
+        Sh.uw[u0 + kBB * h] = w[h];
     }
-    const bool ok = bw_wait_slots<kH>(bw, f, tag, ready, v, ctrl, timeout);
-#pragma unroll
-    for (int h = 0; h < kH; ++h)
-        if (ub + threadIdx.x + (int64_t)kBB * h < ue) Sh.uw[threadIdx.x + kBB * h] = word_value(v[h]);
     if (!ok && lane == 0) Sh.ok = 0;
     __syncthreads();
     if (block_uniform(Sh.ok) == 0) return false;
-    // phase 1 from LDS
+    // phase 1 from LDS: the wave's examples' sums, the step of example j in
+    // lane j, all of them at once, then each entry's step to its occurrence
+    float acc[kG], z = 0.0f;
 #pragma unroll
     for (int j = 0; j < kG; ++j) {
-        if (i0 + wave + (int64_t)kBWaves * j >= i1) break;  // wave-uniform
-        const int k0 = lane, k1 = kWave + lane;
-        float acc = k0 < m[j] ? __builtin_fmaf(Sh.uw[Sh.eu[p[j] + k0]], x[2 * j], 0.0f) : 0.0f;
-        if (k1 < m[j]) acc = __builtin_fmaf(Sh.uw[Sh.eu[p[j] + k1]], x[2 * j + 1], acc);
-        for (int k = 2 * kWave + lane; k < m[j]; k += kWave)
-            acc = __builtin_fmaf(Sh.uw[Sh.eu[p[j] + k]], VAL ? op.val[pb + p[j] + k] : 1.0f, acc);
-        const float yj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(yv), j));
-        const float sj = sgd_scale<LOSS>(wave_sum64(acc), yj, op.lr);
-        if (lane == 0) Sh.s[wave + kBWaves * j] = sj;
+        acc[j] = 0.0f;
+        if (j >= jn) continue;
+        const int m = count(j);
+        const float a0 = Sh.uw[at[2 * j] & 0xFFFF];
+        acc[j] = lane < m ? __builtin_fmaf(a0, VAL ? x[2 * j] : 1.0f, 0.0f) : 0.0f;
+        if (m > kWave) {
+            const float a1 = Sh.uw[at[2 * j + 1] & 0xFFFF];
+            if (kWave + lane < m) acc[j] = __builtin_fmaf(a1, VAL ? x[2 * j + 1] : 1.0f, acc[j]);
+            for (int k = 2 * kWave + lane; k < m; k += kWave)
+                acc[j] = __builtin_fmaf(Sh.uw[Sh.eu[first(j) + k] & 0xFFFF],
+                                        VAL ? op.val[pb + first(j) + k] : 1.0f, acc[j]);
+        }
     }
-    __syncthreads();
-    // every occurrence's step, in parallel: the chains below then read one
-    // LDS word per fma, none of which depends on the chain
-    resolve_steps(Sh.oi, Sh.s, pe - pb);
+#pragma unroll
+    for (int j = 0; j < kG; ++j) {
+        if (j >= jn) break;
+        const float zj = wave_sum64(acc[j]);
+        z = lane == j ? zj : z;
+    }
+    const float s = sgd_scale<LOSS>(z, yv, op.lr);
+    float *const step = reinterpret_cast<float *>(Sh.oi);
+#pragma unroll
+    for (int j = 0; j < kG; ++j) {
+        if (j >= jn) break;
+        const int m = count(j);
+        const float sj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), j));
+        if (lane < m) step[at[2 * j] >> 16] = sj;
+        if (m > kWave) {
+            if (kWave + lane < m) step[at[2 * j + 1] >> 16] = sj;
+            for (int k = 2 * kWave + lane; k < m; k += kWave) step[Sh.eu[first(j) + k] >> 16] = sj;
+        }
+    }
     __syncthreads();
     // phase 2 from LDS; the features the next batch waits for are published
     // before the others (one CU issues a batch's thousands of scattered
     // stores, and the waiting batch needs only a few of them)
-    float val[kH];
 #pragma unroll
     for (int h = 0; h < kH; ++h) {
-        val[h] = 0.0f;
-        if (ub + threadIdx.x + (int64_t)kBB * h < ue)
-            val[h] = chain_apply<VAL>(Sh.uw[threadIdx.x + kBB * h],
-                                      reinterpret_cast<const float *>(Sh.oi), Sh.ox, q0[h], q1[h]);
+        if (h >= hn) break;
+        w[h] = chain_apply<VAL>(w[h], step, Sh.ox, qq[h] & 0xFFFF, qq[h] >> 16);
+        if (urgent >> h & 1) word_put(bw, f[h], word_pack(w[h], (int)ub + u0 + kBB * h));
     }
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-#pragma unroll
-        for (int h = 0; h < kH; ++h) {
-            const int64_t u = ub + threadIdx.x + (int64_t)kBB * h;
-            if (u < ue && urgent[h] == (pass == 0)) word_put(bw, f[h], word_pack(val[h], (int)u));
-        }
+    for (int h = 0; h < kH; ++h) {
+        if (h >= hn) break;
+        if (u0 + kBB * h < nU && !(urgent >> h & 1))
+            word_put(bw, f[h], word_pack(w[h], (int)ub + u0 + kBB * h));
     }
     __syncthreads();
     return true;
@@ -660,6 +702,434 @@ __global__ __launch_bounds__(kBB) void k_batch_syncfree(BatchOp<LOSS, VAL> op,
                 return;
         } else {
             if (!general_batch(op, uprev, bw, Sh, i0, i1, pb, pe, ub, ue, ctrl, timeout)) return;
+        }
+    }
+}
+
+// LDS of a batch run example by example (flow_batch).  Per entry, the weight
+// its example reads (until that word is read: the tag it waits for) and a
+// code: its union feature relative to the batch, or, where the feature has
+// several entries in the batch, kFlowMany + a number into the m arrays.  Those hold
+// the feature, its entries' examples and values in example order, and how
+// many of its examples have not run yet.
+struct FlowShared {
+    float w[kFlowCap];
+    uint16_t code[kFlowCap];
+    float s[kFlowB];           // steps by example
+    float mx[kFlowOcc];
+    uint16_t mi[kFlowOcc];
+    uint16_t mfeat[kFlowOcc / 2], mbase[kFlowOcc / 2], mcount[kFlowOcc / 2];
+    int32_t mleft[kFlowOcc / 2];
+    // awaited entries: e | (worker << 4 | its example) << 16
+    int32_t list[kFlowList];
+    int32_t cnt[kFlowWorkers * 16];  // words an example still waits for
+    int32_t ready[kFlowWorkers];     // a worker's examples that wait for none
+    int nm, nocc, np, stop;
+};
+static_assert(2 * kFlowG <= 16 && kFlowWorkers <= 16 && kFlowCap <= 1 << 16, "packing of list");
+
+// The batch's structure into LDS, none of it dependent on earlier batches.
+// False when too many entries share their feature.
+template <int LOSS, bool VAL>
+__device__ bool flow_stage(const BatchOp<LOSS, VAL> &op, const int32_t *uprev, FlowShared &S,
+                           int64_t i0, int64_t pb, int64_t ub, int64_t ue) {
+    if (threadIdx.x == 0) S.nm = S.nocc = 0;
+    __syncthreads();
+    // kH union features per thread at a time, each of their loads in flight
+    // together
+    for (int64_t u0 = ub + threadIdx.x; u0 < ue; u0 += kCap) {
+        int32_t a[kH], z[kH], e[kH], tag[kH];
+#pragma unroll
+        for (int h = 0; h < kH; ++h) {
+            const int64_t u = min(u0 + (int64_t)kBB * h, ue - 1);
+            a[h] = (int32_t)op.uptr[u];  // nnz < 2^31
+            z[h] = (int32_t)op.uptr[u + 1];
+            tag[h] = uprev[u];
+        }
+#pragma unroll
+        for (int h = 0; h < kH; ++h) e[h] = op.occ[a[h]] - (int32_t)pb;
+#pragma unroll
+        for (int h = 0; h < kH; ++h) {
+            const int64_t u = u0 + (int64_t)kBB * h;
+            if (u >= ue) break;
+            const int n = z[h] - a[h];
+            if (n == 1) {
+                S.code[e[h]] = (uint16_t)(u - ub);
+                S.w[e[h]] = __int_as_float(tag[h]);
+                continue;
+            }
+            const int base = atomicAdd(&S.nocc, n);
+            if (base + n > kFlowOcc) continue;  // seen below
+            const int mid = atomicAdd(&S.nm, 1);
+            S.mfeat[mid] = (uint16_t)(u - ub);
+            S.mbase[mid] = (uint16_t)base;
+            S.mcount[mid] = (uint16_t)n;
+            S.mleft[mid] = n;
+            for (int k = 0; k < n; ++k) {
+                const int32_t q = op.occ[a[h] + k];
+                S.code[q - (int32_t)pb] = (uint16_t)(kFlowMany + mid);
+                S.w[q - (int32_t)pb] = __int_as_float(tag[h]);
+                S.mi[base + k] = (uint16_t)(op.occ_row[a[h] + k] - (int32_t)i0);
+                S.mx[base + k] = VAL ? op.val[q] : 1.0f;
+            }
+        }
+    }
+    __syncthreads();
+    return block_uniform(S.nocc) <= kFlowOcc;
+}
+
+// the wave's number in the block, wave-uniform for the compiler too: the waves'
+// roles then are scalar branches, and neither role keeps the other's registers
+__device__ __forceinline__ int flow_wave() {
+    return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+
+// v, opaque to the compiler: what is computed from it is computed where it is
+// used and not kept in registers from the start
+__device__ __forceinline__ int here(int v) {
+    __asm__ volatile("" : "+v"(v));
+    return v;
+}
+
+// words by 32-bit byte offset (one scalar base for every access)
+__device__ __forceinline__ unsigned long long flow_get(const unsigned long long *bw, unsigned off) {
+    return __hip_atomic_load(reinterpret_cast<const unsigned long long *>(
+                                 reinterpret_cast<const char *>(bw) + (size_t)(unsigned)here((int)off)),
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void flow_put(unsigned long long *bw, unsigned off,
+                                         unsigned long long w) {
+    __hip_atomic_store(
+        reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(bw) +
+                                               (size_t)(unsigned)here((int)off)),
+        w,
+        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A worker: examples g + wave + kFlowWorkers j, j < G.
+template <int LOSS, bool VAL, int G>
+struct FlowWorker {
+    int rel, num;  // lane j: first entry (relative to the batch's) and entry count of example j
+    float y;       // lane j: its label
+    unsigned c[2 * G];  // entry 64 h + lane of example j at t = 2 j + h: its word's offset, value
+    // stored values: kept where they fit the registers, else read again by run()
+    static constexpr bool kKeep = VAL && G <= kFlowG;
+    float x[kKeep ? 2 * G : 1];
+    unsigned todo;  // examples still to run (wave-uniform)
+
+    __device__ __forceinline__ int first(int j) const { return __builtin_amdgcn_readlane(rel, j); }
+    __device__ __forceinline__ int count(int j) const { return __builtin_amdgcn_readlane(num, j); }
+
+    // this lane's value of example j's entry 64 h + lane (which exists)
+    __device__ __forceinline__ float value(const BatchOp<LOSS, VAL> &op, int64_t pb, int j,
+                                           int h) const {
+        if constexpr (kKeep) return x[2 * j + h];
+        if constexpr (VAL) return op.val[pb + first(j) + h * kWave + lane_id()];
+        return 1.0f;
+    }
+
+    // returns the lane's live entries as a bit mask
+    __device__ __forceinline__ unsigned load(const BatchOp<LOSS, VAL> &op, int64_t g, int64_t i1,
+                                             int64_t pb) {
+        const int lane = lane_id();
+        const int64_t i = g + flow_wave() + (int64_t)kFlowWorkers * lane;
+        const bool has = lane < G && i < i1;
+        const int64_t rb = op.row_ptr[has ? i : g];
+        num = has ? (int)(op.row_ptr[i + 1] - rb) : 0;
+        rel = (int)(rb - pb);
+        y = op.y[has ? i : g];
+        todo = (unsigned)__ballot(has);
+        unsigned live = 0;
+#pragma unroll
+        for (int t = 0; t < 2 * G; ++t) {
+            const int k = (t & 1) * kWave + lane;
+            const bool lv = k < count(t >> 1);
+            const int64_t e = pb + first(t >> 1) + k;
+            live |= lv ? 1u << t : 0u;
+            c[t] = lv ? 8u * (unsigned)op.col[e] : 0u;
+            if constexpr (kKeep) x[t] = lv ? op.val[e] : 1.0f;
+        }
+        return live;
+    }
+
+    // reads the words of the lane's entries in `pend`; those that carry their
+    // tag go to LDS, the others are returned
+    __device__ __forceinline__ unsigned read(unsigned long long *bw, FlowShared &S, unsigned pend) {
+        const int lane = lane_id();
+        constexpr int kC = 8;  // words in flight per lane
+#pragma unroll
+        for (int t0 = 0; t0 < 2 * G; t0 += kC) {
+            if (__ballot(pend >> t0 & ((1u << kC) - 1)) == 0ull) continue;
+            unsigned long long v[kC];
+#pragma unroll
+            for (int k = 0; k < kC; ++k)
+                if (pend >> (t0 + k) & 1) v[k] = flow_get(bw, c[t0 + k]);
+#pragma unroll
+            for (int k = 0; k < kC; ++k) {
+                const int t = t0 + k;
+                if (pend >> t & 1) {
+                    float &w = S.w[first(t >> 1) + here((t & 1) * kWave + lane)];
+                    if (word_tag(v[k]) == __float_as_int(w)) {
+                        w = word_value(v[k]);
+                        pend &= ~(1u << t);
+                    }
+                }
+            }
+        }
+        return pend;
+    }
+
+    // lists the awaited entries from list position `at` on, counts them per
+    // example and marks the examples that wait for none
+    __device__ __forceinline__ void list(FlowShared &S, unsigned pend, int at) {
+        const int lane = lane_id(), wave = flow_wave();
+        int mine = 0;
+#pragma unroll
+        for (int t = 0; t < 2 * G; ++t) {
+            const unsigned long long bal = __ballot(pend >> t & 1);
+            if (pend >> t & 1)
+                S.list[at + (int)lanes_below(bal)] =
+                    (first(t >> 1) + (t & 1) * kWave + lane) | (wave << 4 | t >> 1) << 16;
+            at += __popcll(bal);
+            mine += lane == t >> 1 ? __popcll(bal) : 0;
+        }
+        if (lane < G) S.cnt[wave * 16 + lane] = mine;
+        const unsigned none = (unsigned)__ballot(mine == 0) & todo;
+        if (lane == 0) S.ready[wave] = (int)none;
+    }
+
+    // Runs the examples in `ready`: their sums, then lane j takes example j's step
+    // (all lanes at once), then their entries' new weights.
+    __device__ __forceinline__ void run(const BatchOp<LOSS, VAL> &op, unsigned long long *bw,
+                                        FlowShared &S, unsigned ready, int ex0, int64_t pb, int ub) {
+        const int lane = lane_id();
+        float z = 0.0f;
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            if (!(ready >> j & 1)) continue;
+            const int p = here(first(j)), m = count(j);
+            float acc = 0.0f;
+            if (lane < m) acc = __builtin_fmaf(S.w[p + lane], value(op, pb, j, 0), 0.0f);
+            if (kWave + lane < m)
+                acc = __builtin_fmaf(S.w[p + kWave + lane], value(op, pb, j, 1), acc);
+            const float zj = wave_sum64(acc);
+            z = lane == j ? zj : z;
+        }
+        const float s = sgd_scale<LOSS>(z, y, op.lr);
+        if (lane < G && (ready >> lane & 1)) S.s[ex0 + kFlowWorkers * lane] = s;
+        __asm__ __volatile__("" ::: "memory");
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            if (!(ready >> j & 1)) continue;
+            const float sj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), j));
+            const int p = here(first(j)), m = count(j);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int k = h * kWave + lane;
+                if (k >= m) continue;
+                const float w = S.w[p + k];
+                int f = S.code[p + k];
+                float nv = __builtin_fmaf(-sj, value(op, pb, j, h), w);
+                if (f >= kFlowMany) {
+                    // LDS runs one wave's operations in order: the step is
+                    // there before the count says so
+                    const int mid = f - kFlowMany;
+                    if (atomicSub(&S.mleft[mid], 1) != 1) continue;
+                    __asm__ __volatile__("" ::: "memory");
+                    const int q0 = S.mbase[mid], n = S.mcount[mid];
+                    nv = w;
+                    for (int q = q0; q < q0 + n; ++q)
+                        nv = __builtin_fmaf(-S.s[S.mi[q]], S.mx[q], nv);
+                    f = S.mfeat[mid];
+                }
+                flow_put(bw, c[2 * j + h], word_pack(nv, ub + f));
+            }
+        }
+    }
+};
+
+// A poller: waits for its share of the listed words, puts each into LDS as it
+// comes and hands an example to its worker with its last one.
+template <int LOSS, bool VAL>
+__device__ void flow_poll(const BatchOp<LOSS, VAL> &op, unsigned long long *bw, FlowShared &S,
+                          int64_t pb, int np, Ctrl *ctrl, int64_t timeout) {
+    const int lane = lane_id();
+    const int first = (flow_wave() - kFlowWorkers) * kWave + lane;
+    int le[kFlowSlots], lt[kFlowSlots];
+    unsigned lc[kFlowSlots];
+    unsigned lp = 0;  // bit k: the lane awaits its k-th word
+#pragma unroll
+    for (int k = 0; k < kFlowSlots; ++k) {
+        const int r = first + k * kFlowPollers * kWave;
+        const bool in = r < np;
+        le[k] = in ? S.list[r] : 0;
+        lc[k] = in ? 8u * (unsigned)op.col[pb + (le[k] & 0xFFFF)] : 0u;
+        lt[k] = in ? __float_as_int(S.w[le[k] & 0xFFFF]) : 0;
+        lp |= in ? 1u << k : 0u;
+    }
+    int64_t t0 = now_ticks();  // last time the watchdog saw a word come
+    unsigned seen = lp;
+    for (int round = 0; __ballot(lp != 0) != 0ull; ++round) {
+        if ((round & 31) == 31) {
+            const int64_t t = now_ticks();
+            if (__ballot(seen != lp) != 0ull) t0 = t;
+            seen = lp;
+            const bool late = t - t0 > timeout;
+            if (late) record_error(ctrl, DERR_WAIT_TIMEOUT);
+            if (late || aborted(ctrl)) {
+                S.stop = 1;
+                return;
+            }
+        }
+        constexpr int kC = 8;
+#pragma unroll
+        for (int k0 = 0; k0 < kFlowSlots; k0 += kC) {
+            if (__ballot(lp >> k0 & ((1u << kC) - 1)) == 0ull) continue;
+            __asm__ __volatile__("" ::: "memory");  // the loads below are issued again
+            unsigned long long v[kC];
+#pragma unroll
+            for (int k = 0; k < kC; ++k)
+                if (lp >> (k0 + k) & 1) v[k] = flow_get(bw, lc[k0 + k]);
+#pragma unroll
+            for (int i = 0; i < kC; ++i) {
+                const int k = k0 + i;
+                if ((lp >> k & 1) && word_tag(v[i]) == lt[k]) {
+                    lp &= ~(1u << k);
+                    S.w[here(le[k]) & 0xFFFF] = word_value(v[i]);
+                    __asm__ __volatile__("" ::: "memory");  // LDS runs one wave's operations in order
+                    const int ex = here(le[k]) >> 16;
+                    if (atomicSub(&S.cnt[ex], 1) == 1) atomicOr(&S.ready[ex >> 4], 1 << (ex & 15));
+                }
+            }
+        }
+    }
+}
+
+// Examples g .. (up to kFlowWorkers * G of them) of a staged batch.
+// False when a wait gave up; every thread of the block returns the same.
+template <int LOSS, bool VAL, int G>
+__device__ bool flow_group(const BatchOp<LOSS, VAL> &op, unsigned long long *bw, FlowShared &S,
+                           int64_t i0, int64_t g, int64_t i1, int64_t pb, int64_t ub, Ctrl *ctrl,
+                           int64_t timeout) {
+    const int wave = flow_wave();
+    const bool worker = wave < kFlowWorkers;
+    FlowWorker<LOSS, VAL, G> W;
+    unsigned pend = 0;
+    if (worker) pend = W.load(op, g, i1, pb);
+    if (threadIdx.x == 0) S.np = S.stop = 0;
+    __syncthreads();
+    // every word once (again while more of them are awaited than the list holds)
+    const int64_t t0 = now_ticks();
+    int at = 0, np = 0;
+    for (;;) {
+        if (worker) {
+            pend = W.read(bw, S, pend);
+            int n = 0;
+#pragma unroll
+            for (int t = 0; t < 2 * G; ++t) n += __popcll(__ballot(pend >> t & 1));
+            if (lane_id() == 0) at = atomicAdd(&S.np, n);
+            at = __builtin_amdgcn_readfirstlane(at);
+        }
+        __syncthreads();
+        np = block_uniform(S.np);
+        if (np <= kFlowList) break;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            S.np = 0;
+            const bool late = now_ticks() - t0 > timeout;
+            if (late) record_error(ctrl, DERR_WAIT_TIMEOUT);
+            if (late || aborted(ctrl)) S.stop = 1;
+        }
+        __syncthreads();
+        if (block_uniform(S.stop)) return false;
+    }
+    if (worker) W.list(S, pend, at);
+    __syncthreads();
+    if (worker) {
+        const int ex0 = (int)(g - i0) + wave;
+        for (int spin = 0; W.todo;) {
+            const unsigned r = (unsigned)__builtin_amdgcn_readfirstlane(
+                __hip_atomic_load(&S.ready[wave], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+            const unsigned ready = r & W.todo;
+            if (ready) {
+                __builtin_amdgcn_s_setprio(2);
+                __asm__ __volatile__("" ::: "memory");
+                W.run(op, bw, S, ready, ex0, pb, (int)ub);
+                W.todo &= ~ready;
+                __builtin_amdgcn_s_setprio(0);
+                spin = 0;
+                continue;
+            }
+            if ((++spin & 15) == 0 &&
+                __builtin_amdgcn_readfirstlane(__hip_atomic_load(
+                    &S.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)))
+                break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+    } else {
+        __builtin_amdgcn_s_setprio(1);
+        flow_poll<LOSS, VAL>(op, bw, S, pb, np, ctrl, timeout);
+        __builtin_amdgcn_s_setprio(0);
+    }
+    __syncthreads();
+    return block_uniform(S.stop) == 0;
+}
+
+// Sync-free epoch where a batch's features mostly have one entry each: batches
+// run example by example.  An example runs as soon as its own words carry
+// their previous union entries, not when the whole batch's do, so a hand-over
+// between batches costs one device-scope hop and one example's arithmetic, and
+// only examples that share a feature wait for each other: the chain is 2,738
+// hops long where 5,000 batches of 100 examples of 80 uniform features over
+// 2 million form a chain of 5,000 whole batches (94 -> 8.8 ms; batches of
+// 200: 285 -> 20.8 ms).  An entry that is its feature's only one in the batch
+// publishes the new weight at once (no other example of the batch reads it);
+// of several, the example that gets there last applies all of them in example
+// order and publishes.  Nothing in a batch waits for the same batch, so the
+// earliest unfinished batch always makes progress.
+//
+// The block's waves split into workers and pollers: vector memory operations
+// complete in order, so a wave that both published and polled would see its
+// next words only after its stores were acknowledged (10.3 ms with sixteen
+// waves that each did both).  A worker reads its examples' words once, then
+// touches only LDS and its registers until it publishes.
+template <int LOSS, bool VAL, int G>
+__global__ __launch_bounds__(kBB) void k_batch_flow(BatchOp<LOSS, VAL> op,
+                                                   const int32_t *__restrict__ uprev,
+                                                   unsigned long long *bw, int64_t nb, Ctrl *ctrl,
+                                                   int64_t timeout) {
+    __shared__ union {
+        SfShared g;
+        FlowShared f;
+    } Sh;
+    __shared__ int64_t s_ticket;
+    __shared__ int s_long;
+    for (;;) {
+        if (threadIdx.x == 0) {
+            s_ticket = (int64_t)atomicAdd(&ctrl->ticket, 1ull);
+            s_long = 0;
+        }
+        __syncthreads();
+        const int64_t b = block_uniform64(s_ticket);
+        if (b >= nb) return;
+        const int64_t i0 = b * op.B, i1 = min(i0 + op.B, op.n);
+        const int64_t pb = op.row_ptr[i0], pe = op.row_ptr[i1];
+        const int64_t ub = op.bptr[b], ue = op.bptr[b + 1];
+        bool fits = pe - pb <= kFlowCap && i1 - i0 <= kFlowB;
+        if (fits) {
+            const int64_t i = i0 + threadIdx.x;
+            if (i < i1 && op.row_ptr[i + 1] - op.row_ptr[i] > 2 * kWave) s_long = 1;
+            fits = flow_stage<LOSS, VAL>(op, uprev, Sh.f, i0, pb, ub, ue);
+            fits = fits && block_uniform(s_long) == 0;
+            __syncthreads();
+        }
+        if (fits) {
+            for (int64_t g = i0; g < i1; g += kFlowWorkers * G)
+                if (!flow_group<LOSS, VAL, G>(op, bw, Sh.f, i0, g, i1, pb, ub, ctrl, timeout)) return;
+        } else {
+            if (threadIdx.x == 0) Sh.g.ok = 1;
+            __syncthreads();
+            if (!general_batch(op, uprev, bw, Sh.g, i0, i1, pb, pe, ub, ue, ctrl, timeout)) return;
         }
     }
 }
@@ -708,7 +1178,8 @@ int64_t batch_sf_ws_bytes(int64_t d) { return (int64_t)sizeof(Ctrl) + align_up(8
 
 template <int LOSS, bool VAL>
 int launch_batch_syncfree(const BatchOp<LOSS, VAL> &op, const pdb_levels *lv, int64_t d,
-                          int64_t nb, void *ws, const Opts &opt, hipStream_t s) {
+                          int64_t nb, int64_t nnz, int64_t U, void *ws, const Opts &opt,
+                          hipStream_t s) {
     Ctrl *ctrl = static_cast<Ctrl *>(ws);
     unsigned long long *bw =
         reinterpret_cast<unsigned long long *>(static_cast<char *>(ws) + sizeof(Ctrl));
@@ -728,7 +1199,27 @@ int launch_batch_syncfree(const BatchOp<LOSS, VAL> &op, const pdb_levels *lv, in
     // that slow the frontier's memory accesses
     const int64_t cap = opt.batch_sf_blocks;
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(cus, cap), nb));
-    k_batch_syncfree<LOSS, VAL><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, ctrl, timeout);
+    // Example by example where few entries share their feature with another of
+    // the batch, else a batch at a time.  The line: at 3.6% of the entries the
+    // two take about the same (16.7 ms a batch at a time, 15.7 ms by example,
+    // 200,000 examples of 30 uniform features over 20,000, batches of 50), at
+    // 1.4% 16.8 and 8.2 ms, at 5.8% 20.9 and 26.9 ms, at 58% (Zipf 1.2) 25 and
+    // 87 ms.  A block takes one batch, so batches of fewer examples than about
+    // half a block's waves leave it idle (50,000 examples of 80 features over
+    // 2 million, a batch at a time and by example: batches of 4 3.1 and 3.8 ms,
+    // of 8 4.4 and 2.3 ms).  It addresses words with 32-bit byte offsets.
+    const bool flow = U > 0 && 32 * (nnz - U) <= nnz && op.B >= 8 && op.B <= kFlowB &&
+                      d <= int64_t(1) << 28;
+    // the most examples per worker that a batch needs, so that they are all in
+    // flight together: with half as many, batches of 128 took 50 ms, not 15.7
+    if (!flow)
+        k_batch_syncfree<LOSS, VAL><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, ctrl, timeout);
+    else if (op.B <= kFlowWorkers * kFlowG)
+        k_batch_flow<LOSS, VAL, kFlowG><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, ctrl,
+                                                             timeout);
+    else
+        k_batch_flow<LOSS, VAL, 2 * kFlowG><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, ctrl,
+                                                                 timeout);
     PDB_LAUNCHED();
     if (d > 0) {
         k_bw_out<<<grid_for(d, kBlock, 8192), kBlock, 0, s>>>(bw, op.w, d);
@@ -869,7 +1360,7 @@ extern "C" int pdb_batch_epoch(const pdb_csr *csr, const float *labels, int64_t 
                     BatchOp<LOSS, VAL>{csr->row_ptr, csr->col, csr->val, labels, w, bt->bptr,   \
                                        bt->ucol, bt->uptr, bt->occ, bt->occ_row, bt->occ_u,         \
                                        bt->unext, n, batch, lr}, \
-                    lv, d, nb, ws, o, s)                                                        \
+                    lv, d, nb, nnz, bt->U_host, ws, o, s)                                                        \
               : launch_batch<LOSS, VAL>(                                                       \
                     BatchOp<LOSS, VAL>{csr->row_ptr, csr->col, csr->val, labels, w, bt->bptr,   \
                                        bt->ucol, bt->uptr, bt->occ, bt->occ_row, bt->occ_u,         \

@@ -2,6 +2,8 @@
 pdb_batch_epoch) against the CPU oracle on the same seeded inputs: the batch
 unions, occurrence lists, batch levels and grouping bit-exact; weights bitwise
 equal to the oracle's matched order and within 1e-5 of its natural order."""
+import random
+
 import numpy as np
 import pytest
 
@@ -212,3 +214,33 @@ def test_full_size_batch_levels(gpu, cfg):
     g = batch_workload(datagen.generate(cfg), 100)
     bt, lv = check_batch_schedule(native, gpu, g["row_ptr"], g["col"], g["d"], 100)
     check_batch_epoch(native, gpu, g, 100, bt, lv, opt=dict(epoch_mode=1))
+
+
+# Batches whose features mostly have one entry each (at most one entry in 32
+# shares its feature with another of its batch) run example by example.  Edges:
+# examples per worker and per block (104, 208, 256), entries per example (0,
+# 64, 128) and per batch (16384), entries on shared features of one batch
+# (4096); beyond the last four a batch runs by itself as a whole.
+@pytest.mark.parametrize("B,extra", [(8, ""), (13, ""), (104, ""), (105, ""), (208, ""),
+                                     (209, ""), (256, "big"), (100, "long"), (100, "shared")])
+@pytest.mark.parametrize("loss,with_val", [(0, False), (1, True)])
+def test_batches_example_by_example(gpu, B, extra, loss, with_val):
+    native = native_mod()
+    rng = np.random.default_rng(B)
+    sample = random.Random(B).sample
+    n, d = 1800, 600_000
+    lengths = rng.choice([0, 1, 5, 63, 64, 65, 100, 127, 128], n)
+    if extra == "big":
+        lengths[256:512] = 70  # 17920 entries in the second batch
+    rows = [set(sample(range(d), int(m))) for m in lengths]
+    if extra == "long":
+        rows[350] = set(sample(range(d), 129))
+    if extra == "shared":
+        n = 3000  # few shared features overall, 4500 entries on 45 of them in one batch
+        rows += [set(sample(range(d), 100)) for _ in range(1200)]
+        for i in range(700, 800):
+            rows[i] = set(range(45))
+    g = structured_problem(rows, loss, with_val, 5 + B, B)
+    bt, lv = check_batch_schedule(native, gpu, g["row_ptr"], g["col"], g["d"], B)
+    assert 32 * (len(g["col"]) - bt.U_host) <= len(g["col"])
+    check_batch_epoch(native, gpu, g, B, bt, lv)
