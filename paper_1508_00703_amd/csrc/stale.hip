@@ -14,11 +14,12 @@
 //
 // Windowed (one block): examples in windows of W = delay + 1.  Every read
 // of window k has its source in window k - 1 or earlier, so the block holds
-// the values written by window k - 1 in LDS and the state before it in w:
-// it loads window k's reads, commits window k - 1's last writes to w, forms
-// the W steps (a wave per example), then runs each feature's writes through
-// the window in example order from its first entry.  Chosen when a window's
-// entries fit the block's LDS.
+// the values written by the last windows in LDS and older ones in w: it takes
+// window k's reads, forms the W steps (a wave per example), then runs each
+// feature's writes through the window in example order.  Chosen when a
+// window's entries fit the block's LDS.  Passes over all windows before it lay
+// every window's entries out by feature, in example order (an entry's place),
+// so that a feature's chain is a stretch of consecutive places.
 //
 // Sync-free (otherwise): every stored entry owns a 64-bit word (the value it
 // wrote, its own index as the tag); waves take examples in index order; an
@@ -39,7 +40,6 @@ constexpr int kSWaves = kBlock / kWave;
 constexpr int kWinCap = 2048;          // entries (and examples) of a window held in LDS
 constexpr int kWinThreads = 1024;
 constexpr int kWinWaves = kWinThreads / kWave;
-constexpr int kWinPer = kWinCap / kWinThreads;  // entries per thread
 
 struct StaleWs {
     Ctrl *ctrl;
@@ -72,23 +72,11 @@ StaleWs stale_layout(void *base, int64_t nnz) {
 }
 
 __global__ void k_stale_clear(unsigned long long *__restrict__ words,
-                              int32_t *__restrict__ overwritten, int32_t *__restrict__ next,
-                              int64_t nnz) {
+                              int32_t *__restrict__ overwritten, int64_t nnz) {
     for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < nnz;
          q += (int64_t)gridDim.x * blockDim.x) {
         words[q] = word_pack(0.0f, -1);
         overwritten[q] = 0;
-        next[q] = -1;
-    }
-}
-
-// next writer: the entry whose previous entry on the feature is q
-__global__ void k_stale_next(const int32_t *__restrict__ prev, int64_t nnz,
-                             int32_t *__restrict__ next) {
-    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < nnz;
-         q += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t p = prev[q];
-        if (p >= 0) next[p] = (int32_t)q;
     }
 }
 
@@ -223,172 +211,565 @@ __global__ __launch_bounds__(kBlock) void k_stale_epoch(
     }
 }
 
-// The windowed execution, one block of kWinThreads threads.  Thread t
-// handles entries t and t + kWinThreads of every window, and examples t and
-// t + kWinThreads.  What a window reads from memory that earlier windows do
-// not change (columns, values, read sources, previous and next writers, row
-// bounds, labels) is loaded two windows ahead into registers; the weights it
-// reads from w are loaded one window ahead, right after the commit that
-// makes w the state they need.
-struct WinBuf {
-    int32_t col[kWinCap];
-    float x[kWinCap];
-    float rv[kWinCap];     // the value the entry reads
-    float v[kWinCap];      // the value the entry writes
-    int32_t nxt[kWinCap];  // next entry on the feature (CSR index), -1 = none
-    int16_t ex[kWinCap];   // the entry's example within the window
-    int32_t rp[kWinCap + 1];  // example bounds, relative to the window's first entry
-    float y[kWinCap];
+// Windowed, pass 1: read sources as k_stale_sources finds them, and each
+// entry's chain in its window: the first entry on its feature (the head) and
+// how many lie before it.  One wave per example; at most `delay` steps back.
+__global__ __launch_bounds__(kBlock) void k_win_chains(const int64_t *__restrict__ row_ptr,
+                                                       int64_t n,
+                                                       const int32_t *__restrict__ prev,
+                                                       int64_t delay, int64_t W,
+                                                       int32_t *__restrict__ rd,
+                                                       unsigned long long *__restrict__ chain) {
+    const int lane = lane_id();
+    const int64_t nw = (int64_t)gridDim.x * kSWaves;
+    for (int64_t a = blockIdx.x * (int64_t)kSWaves + wave_in_block(); a < n; a += nw) {
+        const int64_t b = row_ptr[a], e = row_ptr[a + 1], qw = row_ptr[a / W * W];
+        const bool all_in_window = a - delay <= 0;
+        const int64_t lim = all_in_window ? 0 : row_ptr[a - delay];
+        for (int64_t q = b + lane; q < e; q += kWave) {
+            int32_t k = prev[q], head = (int32_t)q;
+            int rank = 0;
+            while (k >= 0 && (int64_t)k >= lim) {  // lim <= qw
+                if ((int64_t)k >= qw) {
+                    head = k;
+                    ++rank;
+                }
+                k = prev[k];
+            }
+            rd[q] = all_in_window ? -1 : k;
+            chain[q] = (unsigned long long)(unsigned)rank << 32 | (unsigned)head;
+        }
+    }
+}
+
+// Pass 2, one block per window: places 0 .. E - 1, each chain's consecutive;
+// place[q] = the entry's place | its chain's length << kPlaceShift at a head.
+// chain[q] becomes the window's first entry, and above it the slot of the
+// entry's value in the LDS ring of k_stale_window.
+constexpr int kPlaceShift = 11;
+static_assert(kWinCap <= 1 << kPlaceShift, "a place fits below kPlaceShift");
+constexpr int kWinV = 8192;  // values in the LDS ring: the last four windows at least
+static_assert(kWinV >= 4 * kWinCap, "see k_stale_window");
+
+__global__ __launch_bounds__(kBlock) void k_win_places(const int64_t *__restrict__ row_ptr,
+                                                       int64_t n, int64_t W,
+                                                       unsigned long long *__restrict__ chain,
+                                                       int32_t *__restrict__ place) {
+    __shared__ int32_t s_len[kWinCap], s_base[kWinCap];
+    __shared__ int32_t s_next;
+    for (int64_t k = blockIdx.x; k < cdiv_dev(n, W); k += gridDim.x) {
+        const int64_t q0 = row_ptr[k * W];
+        const int E = (int)(row_ptr[min(n, (k + 1) * W)] - q0);
+        for (int e = threadIdx.x; e < E; e += kBlock) s_len[e] = 0;
+        if (threadIdx.x == 0) s_next = 0;
+        __syncthreads();
+        for (int e = threadIdx.x; e < E; e += kBlock) {
+            const unsigned long long c = chain[q0 + e];
+            atomicMax(&s_len[(int)((int64_t)(unsigned)c - q0)], (int)(c >> 32) + 1);
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < E; e += kBlock)
+            if (s_len[e] > 0) s_base[e] = atomicAdd(&s_next, s_len[e]);
+        __syncthreads();
+        for (int e = threadIdx.x; e < E; e += kBlock) {
+            const unsigned long long c = chain[q0 + e];
+            const int at = s_base[(int)((int64_t)(unsigned)c - q0)] + (int)(c >> 32);
+            place[q0 + e] = at | s_len[e] << kPlaceShift;
+            chain[q0 + e] = (unsigned long long)((q0 + at) & (kWinV - 1)) << 32 | (unsigned)q0;
+        }
+        __syncthreads();
+    }
+}
+
+// Pass 3: where the weight the entry reads comes from, in the low half, and
+// at a chain's head where the value before the chain does, in the high half:
+// kInRing | the slot in the LDS ring of values, or 0: from w (the head: from
+// where the read does).  A slot holds its value as long as no more than kWinV
+// entries lie from its window's first to the last of this one.
+constexpr int kInRing = kWinV;
+static_assert(2 * kInRing <= 1 << 15, "two halves");
+
+__global__ __launch_bounds__(kBlock) void k_win_from(const int64_t *__restrict__ row_ptr, int64_t n,
+                                                     int64_t W, const int32_t *__restrict__ prev,
+                                                     const int32_t *__restrict__ rd,
+                                                     const unsigned long long *__restrict__ chain,
+                                                     int32_t *__restrict__ from) {
+    const int lane = lane_id();
+    const int64_t nw = (int64_t)gridDim.x * kSWaves;
+    for (int64_t a = blockIdx.x * (int64_t)kSWaves + wave_in_block(); a < n; a += nw) {
+        const int64_t b = row_ptr[a], e = row_ptr[a + 1], k = a / W;
+        const int64_t qk = row_ptr[k * W], q1 = row_ptr[max(k - 1, (int64_t)0) * W];
+        const int64_t qe = row_ptr[min(n, (k + 1) * W)];
+        for (int64_t q = b + lane; q < e; q += kWave) {
+            const int64_t r = rd[q], pv = prev[q];
+            int f = 0;
+            if (r >= 0) {
+                const unsigned long long c = chain[r];
+                if (qe - (int64_t)(unsigned)c <= kWinV) f = kInRing | (int)(c >> 32);
+            }
+            if (pv >= q1 && pv < qk) f |= (kInRing | (int)(chain[pv] >> 32)) << 16;
+            from[q] = f;
+        }
+    }
+}
+
+// The windowed execution, one block.  The chain of windows is what it costs,
+// so the waves that run it touch no memory but LDS and their stores to w:
+//  * kWinProd producer waves stage the windows in turn, as far ahead as the
+//    staging ring has room: entries by CSR index, values by place, the
+//    weights that come from w.
+//  * A consumer wave takes an example: it reads the weights (from the ring of
+//    values that the last windows wrote, or as staged), sums them, and puts the
+//    step at each entry's place.  After a barrier the consumers take an entry
+//    each; those that head a chain run it over its places, eight reads at a
+//    time, into the ring of values.  After another barrier the next window
+//    goes.
+//  * The last write of each feature of window k goes to w when window k + 1 is
+//    staged (the weights it reads from w are then in LDS).  It is complete
+//    when the wave stores the next window's.  A producer reads w for window
+//    k once every window that is not wholly in the ring of values is complete.
+// A weight comes from w only if its source is not in the ring, which holds the
+// last windows of kWinV entries together, at least three before this one; so
+// no window from k - 3 on wrote it.
+// 200,000 examples of 20-40 entries over 100,000 Zipf-1.1 features, delay 8:
+// 54.0 -> 29 ms (2.4 -> 1.3 us a window of 9); delay 1 42.4 -> 25.7 ms for
+// 50,000, delay 31 8.0 -> 5.8 ms. Before, every wave loaded, staged and waited
+// for memory in every window, and a chain followed its entries' links, two
+// dependent LDS reads each.  With the same data flow but the staging done by
+// all the waves, loads two windows ahead, a window took 2.1 us.  What is left
+// is one wave's issue and LDS latency per window, not memory: the barrier that
+// waits for the stores of a window before, or for several, took the same.
+constexpr int kWinProd = 4;
+constexpr int kWinCons = kWinWaves - kWinProd;
+constexpr int kWinPer = (kWinCap + kWinCons * kWave - 1) / (kWinCons * kWave);  // entries per thread
+constexpr int kWinS = 2 * kWinCap;  // staged entries, and examples
+constexpr int kWinAhead = 16;       // staged windows
+constexpr int kWinU = 6;            // chunks of 64 entries whose loads a producer holds ahead
+
+typedef __attribute__((address_space(3))) float lds_f32;
+
+struct WinShared {
+    float v[kWinV];       // the values the entries wrote, by slot
+    float xp[kWinS + 8];  // by place from the window's first entry on: value (the first 8 again)
+    int32_t place[kWinS], from[kWinS], col[kWinS];  // by entry
+    float wv[kWinS];      // by entry: its feature's weight in w
+    int32_t rb[kWinS];    // by example: first entry
+    float y[kWinS];
+    float st[kWinCap + 8];  // by place: step
+    float sink;
+    int2 win[kWinAhead];  // first entry, last + 1
+    int staged[kWinProd];  // producer: its windows before this one are staged
+    int done;              // windows the consumers are through with
+    int freeq;             // their entries end here
+    int ackq;              // entries of the windows whose writes are in w
+    unsigned arrived;      // consumer waves at the barriers so far
 };
 
-// a window's loads, per thread
-struct WinMeta {
-    int32_t col[kWinPer], rd[kWinPer], pv[kWinPer], nx[kWinPer];
-    float x[kWinPer];
-    int64_t rp[kWinPer + 1];  // row_ptr of examples t, t + kWinThreads (and the end)
-    float y[kWinPer];
+struct WinArgs {
+    const int64_t *row_ptr;
+    const int32_t *col;
+    const float *val, *y;
+    float *w;
+    const int32_t *place, *from;
+    int64_t n, nnz, W;
+    float lr;
+};
+
+__device__ __forceinline__ int win_get(const int *p) {
+    return __builtin_amdgcn_readfirstlane(
+        __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+}
+__device__ __forceinline__ void win_set(int *p, int v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// A barrier of the consumer waves (the producers do not take part), for LDS
+// only, in two halves: the LDS runs each wave's operations in order, so a
+// wave's writes are there once its arrival is counted.
+struct WinBarrier {
+    unsigned passed = 0;  // arrivals of the barriers so far
+    __device__ __forceinline__ void arrive(WinShared &S) {
+        passed += kWinCons;
+        __asm__ __volatile__("" ::: "memory");
+        if (lane_id() == 0) atomicAdd(&S.arrived, 1u);
+        __asm__ __volatile__("" ::: "memory");
+    }
+    __device__ __forceinline__ void wait(WinShared &S) {
+        __asm__ __volatile__("" ::: "memory");
+        while ((int)((unsigned)win_get(reinterpret_cast<const int *>(&S.arrived)) - passed) < 0) {
+        }
+        __asm__ __volatile__("" ::: "memory");
+    }
+};
+
+// loads of kWinU chunks of entries from q on (clamped into the arrays)
+template <bool VAL>
+struct WinChunk {
+    int32_t col[kWinU], place[kWinU], from[kWinU];
+    float x[kWinU];
+    __device__ __forceinline__ void load(const WinArgs &p, int64_t q0) {
+#pragma unroll
+        for (int u = 0; u < kWinU; ++u) {
+            const int64_t q = min(q0 + u * kWave + lane_id(), p.nnz - 1);
+            col[u] = p.col[q];
+            place[u] = p.place[q];
+            from[u] = p.from[q];
+            x[u] = VAL ? p.val[q] : 1.0f;
+        }
+    }
+    // entries q0 .. of the window [qs, qe) into LDS
+    __device__ __forceinline__ void put(WinShared &S, const float *wv, int q0, int qs, int qe) {
+#pragma unroll
+        for (int u = 0; u < kWinU; ++u) {
+            const int q = q0 + u * kWave + lane_id();
+            if (q0 + u * kWave >= qe) break;
+            if (q < qe) {
+                const int i = q & (kWinS - 1);
+                S.col[i] = col[u];
+                S.place[i] = place[u];
+                S.from[i] = from[u];
+                S.wv[i] = wv[u];
+                const int at = (qs + (place[u] & ((1 << kPlaceShift) - 1))) & (kWinS - 1);
+                S.xp[at] = x[u];
+                if (at < 8) S.xp[kWinS + at] = x[u];
+            }
+        }
+    }
 };
 
 template <bool VAL>
-__device__ __forceinline__ void win_load(WinMeta &m, int64_t k, int64_t nwin, int64_t W,
-                                         int64_t n, int64_t nnz, int64_t q0,
-                                         const int64_t *__restrict__ row_ptr,
-                                         const int32_t *__restrict__ col,
-                                         const float *__restrict__ val,
-                                         const float *__restrict__ y,
-                                         const int32_t *__restrict__ prev,
-                                         const int32_t *__restrict__ rd,
-                                         const int32_t *__restrict__ next) {
-    if (k >= nwin) return;
-    const int tid = threadIdx.x;
-    const int64_t a0 = k * W, a1 = min(n, a0 + W);
-#pragma unroll
-    for (int u = 0; u < kWinPer; ++u) {
-        // entries past the window's end are loaded (clamped) and ignored
-        const int64_t q = min(q0 + tid + u * kWinThreads, nnz - 1);
-        if (nnz > 0) {
-            m.col[u] = col[q];
-            m.rd[u] = rd[q];
-            m.pv[u] = prev[q];
-            m.nx[u] = next[q];
-            m.x[u] = VAL ? val[q] : 1.0f;
+__device__ void win_produce(const WinArgs &p, WinShared &S, int id, int64_t nwin) {
+    const int lane = lane_id();
+    auto astart = [&](int64_t k) { return min(p.n, k * p.W); };
+    // first entry of window k, by a vector load: it is waited for when it is
+    // used, not with the next LDS operation
+    auto qstart = [&](int64_t k) {
+        int zero = 0;
+        __asm__ volatile("" : "+v"(zero));
+        return (int32_t)p.row_ptr[astart(k) + zero];  // nnz < 2^31
+    };
+    if (id >= nwin || p.nnz == 0) {
+        // no entries: bounds alone
+        for (int64_t k = id; k < nwin; k += kWinProd) {
+            while (k >= win_get(&S.done) + kWinAhead ||
+                   astart(k + 1) - astart(win_get(&S.done)) > kWinS)
+                __builtin_amdgcn_s_sleep(1);
+            if (lane == 0) S.win[k & (kWinAhead - 1)] = make_int2(0, 0);
+            for (int64_t a = astart(k) + lane; a < astart(k + 1); a += kWave) {
+                S.rb[a & (kWinS - 1)] = 0;
+                S.y[a & (kWinS - 1)] = p.y[a];
+            }
+            __asm__ __volatile__("" ::: "memory");
+            if (lane == 0) win_set(&S.staged[id], (int)k + 1);
         }
-        const int64_t a = min(a0 + tid + u * kWinThreads, a1);
-        m.rp[u] = row_ptr[a];
-        m.y[u] = y[min(a, n - 1)];
+        return;
     }
-    m.rp[kWinPer] = row_ptr[min(a0 + tid + kWinPer * kWinThreads, a1)];
+    // A window's first loads are issued while the producer's window before it
+    // is staged, and its bounds a window before that.  Loads complete in
+    // order: a window's weights are asked for before the next one's first
+    // loads, so that they are not waited for with them.
+    struct Ahead {
+        WinChunk<VAL> c;
+        int32_t rb;
+        float y;
+    } A, B;
+    auto load = [&](Ahead &x, int64_t k, int64_t qs) {
+        x.c.load(p, qs);
+        const int64_t a = min(astart(k) + lane, p.n - 1);
+        x.rb = (int32_t)p.row_ptr[a];
+        x.y = p.y[a];
+    };
+    int64_t qs = __builtin_amdgcn_readfirstlane(qstart(id));
+    int64_t qe = __builtin_amdgcn_readfirstlane(qstart(id + 1));
+    int32_t ns = qstart(id + kWinProd), ne = qstart(id + kWinProd + 1);
+    load(A, id, qs);
+    auto stage = [&](int64_t k, Ahead &cur, Ahead &nxt) {
+        const int64_t a0 = astart(k), a1 = astart(k + 1);
+        // room for its entries, examples and bounds, and nothing to read from
+        // w that is not there yet
+        for (;;) {
+            const int done = win_get(&S.done), freeq = win_get(&S.freeq), ackq = win_get(&S.ackq);
+            if (k < done + kWinAhead && a1 - astart(done) <= kWinS && qe - freeq <= kWinS &&
+                qe - ackq <= kWinV)
+                break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        __asm__ __volatile__("" ::: "memory");
+        float wv[kWinU];
+#pragma unroll
+        for (int u = 0; u < kWinU; ++u)
+            wv[u] = __hip_atomic_load(&p.w[cur.c.col[u]], __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+        const int64_t s1 = __builtin_amdgcn_readfirstlane(ns), e1 = __builtin_amdgcn_readfirstlane(ne);
+        load(nxt, k + kWinProd, s1);
+        ns = qstart(k + 2 * kWinProd);
+        ne = qstart(k + 2 * kWinProd + 1);
+        if (a0 + lane < a1) {
+            S.rb[(a0 + lane) & (kWinS - 1)] = cur.rb;
+            S.y[(a0 + lane) & (kWinS - 1)] = cur.y;
+        }
+        cur.c.put(S, wv, (int)qs, (int)qs, (int)qe);
+        // what is more than a wave's first loads
+        for (int64_t a = a0 + kWave + lane; a < a1; a += kWave) {
+            S.rb[a & (kWinS - 1)] = (int32_t)p.row_ptr[a];
+            S.y[a & (kWinS - 1)] = p.y[a];
+        }
+        for (int64_t q = qs + kWinU * kWave; q < qe; q += kWinU * kWave) {
+            cur.c.load(p, q);
+#pragma unroll
+            for (int u = 0; u < kWinU; ++u)
+                wv[u] = __hip_atomic_load(&p.w[cur.c.col[u]], __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_WORKGROUP);
+            cur.c.put(S, wv, (int)q, (int)qs, (int)qe);
+        }
+        if (lane == 0) S.win[k & (kWinAhead - 1)] = make_int2((int)qs, (int)qe);
+        __asm__ __volatile__("" ::: "memory");  // LDS runs one wave's operations in order
+        if (lane == 0) win_set(&S.staged[id], (int)k + 1);
+        qs = s1;
+        qe = e1;
+    };
+    for (int64_t k = id; k < nwin; k += 2 * kWinProd) {
+        stage(k, A, B);
+        if (k + kWinProd >= nwin) break;
+        stage(k + kWinProd, B, A);
+    }
+}
+
+// What a consumer wave holds of a window before its turn: the bounds, and of
+// its first kWinTurn examples the bounds, the labels (example i's in lane i)
+// and each lane's entry.
+constexpr int kWinTurn = 1;  // three took as long, also where windows hold 16 to 61 examples
+struct WinTurn {
+    int qs, E;
+    float y;
+    int b[kWinTurn], m[kWinTurn];
+    int f[kWinTurn], pl[kWinTurn];  // as S.from (the read) and S.place
+    float wq[kWinTurn], x[kWinTurn];
+};
+
+__device__ __forceinline__ WinTurn win_turn(const WinArgs &p, WinShared &S, int wave, int64_t k) {
+    constexpr int mask = (1 << kPlaceShift) - 1;
+    const int lane = lane_id();
+    WinTurn t;
+    while (win_get(&S.staged[k & (kWinProd - 1)]) <= (int)k) {
+    }
+    __asm__ __volatile__("" ::: "memory");
+    const int2 win = S.win[k & (kWinAhead - 1)];
+    t.qs = __builtin_amdgcn_readfirstlane(win.x);
+    const int qe = __builtin_amdgcn_readfirstlane(win.y);
+    t.E = qe - t.qs;
+    const int64_t a0 = k * p.W;
+    const int nex = (int)(min(p.n, a0 + p.W) - a0), j = kWinCons - 1 - wave;
+    if (j < nex) {
+        const int jl = min(j + min(lane, kWinTurn - 1) * kWinCons, nex - 1);
+        const int bl = S.rb[(a0 + jl) & (kWinS - 1)];
+        const int el = jl + 1 < nex ? S.rb[(a0 + jl + 1) & (kWinS - 1)] : qe;
+        t.y = S.y[(a0 + jl) & (kWinS - 1)];
+#pragma unroll
+        for (int i = 0; i < kWinTurn; ++i) {
+            if (j + i * kWinCons >= nex) break;
+            t.b[i] = __builtin_amdgcn_readlane(bl, i);
+            t.m[i] = __builtin_amdgcn_readlane(el, i) - t.b[i];
+            const int q = (t.b[i] + min(lane, max(t.m[i] - 1, 0))) & (kWinS - 1);
+            t.f[i] = S.from[q];
+            t.pl[i] = S.place[q] & mask;
+            t.wq[i] = S.wv[q];
+            t.x[i] = S.xp[(t.qs + t.pl[i]) & (kWinS - 1)];
+        }
+    }
+    return t;
 }
 
 template <int LOSS, bool VAL>
-__global__ __launch_bounds__(kWinThreads) void k_stale_window(
-    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-    const float *__restrict__ val, const float *__restrict__ y, float *w,
-    const int32_t *__restrict__ prev, const int32_t *__restrict__ rd,
-    const int32_t *__restrict__ next, int64_t n, int64_t nnz, int64_t W, float lr) {
-    __shared__ WinBuf buf[2];
-    __shared__ float S[kWinCap];
-    const int tid = threadIdx.x, lane = lane_id(), wave = wave_in_block();
-    const int64_t nwin = cdiv_dev(n, W);
-    auto qstart = [&](int64_t k) { return row_ptr[min(n, k * W)]; };
-    WinMeta m0, m1, m2;
-    int64_t q0 = qstart(0), q1 = qstart(1), q2 = qstart(2);
-    win_load<VAL>(m0, 0, nwin, W, n, nnz, q0, row_ptr, col, val, y, prev, rd, next);
-    win_load<VAL>(m1, 1, nwin, W, n, nnz, q1, row_ptr, col, val, y, prev, rd, next);
-    float wv[kWinPer];
+__device__ void win_consume(const WinArgs &p, WinShared &S, int wave, int64_t nwin) {
+    constexpr int mask = (1 << kPlaceShift) - 1;
+    const int lane = lane_id(), tid = wave * kWave + lane, w0 = wave * kWave;
+    const unsigned v_a = (unsigned)(uintptr_t)(const lds_f32 *)S.v;
+    const unsigned sink_a = (unsigned)(uintptr_t)(const lds_f32 *)&S.sink;
+    float last_v[kWinPer];
+    int32_t last_c[kWinPer];  // the last writes of the window before
 #pragma unroll
-    for (int u = 0; u < kWinPer; ++u) wv[u] = (nnz > 0) ? w[m0.col[u]] : 0.0f;
-    int cur = 0;
-    int64_t pq0 = 0;  // first entry of the previous window (its end is the current start)
-    int pE = 0;       // entries of the previous window
-    // One window.  mc, mn, mnn: the loads of windows k, k + 1, k + 2 (mnn is
-    // issued here); qa, qb, qc: the first entries of windows k, k + 1, k + 2
-    // (qa receives that of window k + 3).  The three calls per loop
-    // iteration rotate the roles, so no register copy waits on a load still
-    // in flight.
-    auto window = [&](int64_t k, WinMeta &mc, WinMeta &mn, WinMeta &mnn, int64_t &qa,
-                      int64_t qb, int64_t qc) {
-        const int64_t a0 = k * W, a1 = min(n, a0 + W);
-        const int64_t qs = qa;
-        const int E = (int)(qb - qs), nex = (int)(a1 - a0);
-        WinBuf &C = buf[cur];
-        const WinBuf &P = buf[cur ^ 1];
-        // window k into LDS; reads from window k - 1's writes, else from w
-        // as it was before window k - 1
+    for (int u = 0; u < kWinPer; ++u) {
+        last_c[u] = -1;
+        last_v[u] = 0.0f;
+    }
+    int qb = 0;  // first entry of the window before
+    WinBarrier bar;
+    WinTurn T = win_turn(p, S, wave, 0);
+    for (int64_t k = 0; k < nwin; ++k) {
+        const int qs = T.qs, E = T.E;
+        const int64_t a0 = k * p.W;
+        const int nex = (int)(min(p.n, a0 + p.W) - a0);
+        // steps, a wave per example (the last waves first: the first ones head
+        // the chains); dot products in the matched order
+        const int j = kWinCons - 1 - wave;
+        if (j < nex) {
+            float acc[kWinTurn], z = 0.0f;
 #pragma unroll
-        for (int u = 0; u < kWinPer; ++u) {
-            const int e = tid + u * kWinThreads;
-            if (e < E) {
-                const int32_t r = mc.rd[u];
-                C.col[e] = mc.col[u];
-                C.x[e] = mc.x[u];
-                C.nxt[e] = mc.nx[u];
-                C.rv[e] = (r >= pq0) ? P.v[r - pq0] : wv[u];
-            }
-            if (e <= nex) C.rp[e] = (int32_t)(mc.rp[u] - qs);
-            if (e < nex) C.y[e] = mc.y[u];
-        }
-        if (tid + kWinPer * kWinThreads <= nex)
-            C.rp[tid + kWinPer * kWinThreads] = (int32_t)(mc.rp[kWinPer] - qs);
-        __syncthreads();
-        // commit window k - 1: the last write of each feature it touched
-        for (int e = tid; e < pE; e += kWinThreads) {
-            const int32_t nx = P.nxt[e];
-            if (nx < 0 || nx >= qs) w[P.col[e]] = P.v[e];
-        }
-        // window k + 2's loads, in flight while this window computes
-        win_load<VAL>(mnn, k + 2, nwin, W, n, nnz, qc, row_ptr, col, val, y, prev, rd, next);
-        qa = qstart(k + 3);
-        // steps, a wave per example, dot products in the matched order
-        for (int j = wave; j < nex; j += kWinWaves) {
-            const int b = C.rp[j], mm = C.rp[j + 1] - b;
-            float acc = 0.0f;
-            for (int t = lane; t < mm; t += kWave) {
-                acc = __builtin_fmaf(C.rv[b + t], C.x[b + t], acc);
-                C.ex[b + t] = (int16_t)j;
-            }
-            const float z = wave_sum64(acc);
-            if (lane == 0) S[j] = sgd_scale<LOSS>(z, C.y[j], lr);
-        }
-        __syncthreads();
-        // window k + 1's reads of w: w is now the state before window k
-        if (k + 1 < nwin && nnz > 0) {
-#pragma unroll
-            for (int u = 0; u < kWinPer; ++u) wv[u] = w[mn.col[u]];
-        }
-        // writes: each feature's entries of the window in example order,
-        // from the value its previous writer left
-#pragma unroll
-        for (int u = 0; u < kWinPer; ++u) {
-            const int e = tid + u * kWinThreads;
-            const int32_t pv = mc.pv[u];
-            if (e < E && pv < qs) {
-                float v = (pv >= pq0) ? P.v[pv - pq0] : C.rv[e];
-                int ee = e;
-                for (;;) {
-                    v = __builtin_fmaf(-S[C.ex[ee]], C.x[ee], v);
-                    C.v[ee] = v;
-                    const int32_t nx = C.nxt[ee];
-                    if (nx < 0 || nx >= qb) break;
-                    ee = (int)(nx - qs);
+            for (int i = 0; i < kWinTurn; ++i) {
+                if (j + i * kWinCons >= nex) break;
+                const float v = S.v[T.f[i] & (kWinV - 1)];
+                acc[i] = lane < T.m[i]
+                             ? __builtin_fmaf(T.f[i] & kInRing ? v : T.wq[i], T.x[i], 0.0f)
+                             : 0.0f;
+                for (int t = kWave + lane; t < T.m[i]; t += kWave) {
+                    const int q = (T.b[i] + t) & (kWinS - 1);
+                    const int f = S.from[q], pl = S.place[q] & mask;
+                    const float wq = S.wv[q], vr = S.v[f & (kWinV - 1)];
+                    acc[i] = __builtin_fmaf(f & kInRing ? vr : wq, S.xp[(qs + pl) & (kWinS - 1)],
+                                            acc[i]);
                 }
             }
+#pragma unroll
+            for (int i = 0; i < kWinTurn; ++i) {
+                if (j + i * kWinCons >= nex) break;
+                const float zi = wave_sum64(acc[i]);
+                z = lane == i ? zi : z;
+            }
+            const float st = sgd_scale<LOSS>(z, T.y, p.lr);
+#pragma unroll
+            for (int i = 0; i < kWinTurn; ++i) {
+                if (j + i * kWinCons >= nex) break;
+                const float si = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(st), i));
+                if (lane < T.m[i]) S.st[T.pl[i]] = si;
+                for (int t = kWave + lane; t < T.m[i]; t += kWave)
+                    S.st[S.place[(T.b[i] + t) & (kWinS - 1)] & mask] = si;
+            }
         }
-        __syncthreads();
-        pq0 = qs;
-        pE = E;
-        cur ^= 1;
-    };
-    for (int64_t k = 0; k < nwin; k += 3) {
-        window(k, m0, m1, m2, q0, q1, q2);
-        if (k + 1 >= nwin) break;
-        window(k + 1, m1, m2, m0, q1, q2, q0);
-        if (k + 2 >= nwin) break;
-        window(k + 2, m2, m0, m1, q2, q0, q1);
+        // the others of a window of many examples, four of a wave side by side
+        for (int j0 = j + kWinTurn * kWinCons; j0 < nex; j0 += 4 * kWinCons) {
+            float z = 0.0f;
+            const int jl = j0 + lane * kWinCons;  // lane i < 4: example j0 + kWinCons i
+            const bool has = lane < 4 && jl < nex;
+            const int bl = has ? S.rb[(a0 + jl) & (kWinS - 1)] : 0;
+            const int el = has && jl + 1 < nex ? S.rb[(a0 + jl + 1) & (kWinS - 1)] : qs + E;
+            const float yl = has ? S.y[(a0 + jl) & (kWinS - 1)] : 0.0f;
+            int at[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (j0 + i * kWinCons >= nex) break;
+                const int b = __builtin_amdgcn_readlane(bl, i);
+                const int m = __builtin_amdgcn_readlane(el, i) - b;
+                float acc = 0.0f;
+                for (int t0 = 0; t0 < m; t0 += kWave) {
+                    const int t = t0 + lane;
+                    if (t < m) {
+                        const int q = (b + t) & (kWinS - 1);
+                        const int f = S.from[q], pl = S.place[q] & mask;
+                        const float wq = S.wv[q];
+                        const float v = S.v[f & (kWinV - 1)], x = S.xp[(qs + pl) & (kWinS - 1)];
+                        acc = __builtin_fmaf(f & kInRing ? v : wq, x, acc);
+                        if (t0 == 0) at[i] = pl;
+                    }
+                }
+                const float zi = wave_sum64(acc);
+                z = lane == i ? zi : z;
+            }
+            const float st = sgd_scale<LOSS>(z, yl, p.lr);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (j0 + i * kWinCons >= nex) break;
+                const int b = __builtin_amdgcn_readlane(bl, i);
+                const int m = __builtin_amdgcn_readlane(el, i) - b;
+                const float si =
+                    __int_as_float(__builtin_amdgcn_readlane(__float_as_int(st), i));
+                if (lane < m) S.st[at[i]] = si;
+                for (int t = kWave + lane; t < m; t += kWave)
+                    S.st[S.place[(b + t) & (kWinS - 1)] & mask] = si;
+            }
+        }
+        // the writes of window k - 2 are in w; those of window k - 1 go
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        bar.arrive(S);
+#pragma unroll
+        for (int u = 0; u < kWinPer; ++u)
+            if (last_c[u] >= 0)
+                __hip_atomic_store(&p.w[last_c[u]], last_v[u], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+        // the chains' heads, and the value before each
+        int head[kWinPer];
+        float base[kWinPer];
+#pragma unroll
+        for (int u = 0; u < kWinPer; ++u) {
+            head[u] = 0;
+            last_c[u] = -1;
+            base[u] = 0.0f;
+            const int e = tid + u * kWinCons * kWave;
+            if (w0 + u * kWinCons * kWave >= E) continue;
+            const int q = (qs + e) & (kWinS - 1);
+            const int pl = S.place[q], f = S.from[q], c = S.col[q];
+            const float wq = S.wv[q];
+            const float vr = S.v[f & (kWinV - 1)], vh = S.v[f >> 16 & (kWinV - 1)];
+            if (e < E && pl >> kPlaceShift) {
+                head[u] = pl;
+                last_c[u] = c;
+                base[u] = f >> 16 & kInRing ? vh : f & kInRing ? vr : wq;
+            }
+        }
+        bar.wait(S);
+        if (tid == 0) win_set(&S.ackq, qb);
+        // writes: each chain's entries in example order, from the value before
+        // it, eight at a time (reads past its end and past the window's are
+        // not used, writes there go to the sink)
+#pragma unroll
+        for (int u = 0; u < kWinPer; ++u) {
+            if (w0 + u * kWinCons * kWave >= E) continue;
+            const int len = head[u] >> kPlaceShift, a = head[u] & mask;
+            float v = base[u];
+            for (int i = 0; __ballot(i < len) != 0ull; i += 8) {
+                const int ai = min(a + i, kWinCap);
+                const float *const st = &S.st[ai], *const xp = &S.xp[(qs + ai) & (kWinS - 1)];
+                float sv[8], xv[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    sv[t] = st[t];
+                    xv[t] = xp[t];
+                }
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const bool on = i + t < len;
+                    if (t > 0 && __ballot(on) == 0ull) break;
+                    const float nv = __builtin_fmaf(-sv[t], xv[t], v);
+                    v = on ? nv : v;
+                    const unsigned to = on ? v_a + ((qs + a + i + t) & (kWinV - 1)) * 4u : sink_a;
+                    *(lds_f32 *)(uintptr_t)to = v;
+                }
+            }
+            last_v[u] = v;
+        }
+        bar.arrive(S);
+        qb = qs;
+        if (k + 1 < nwin) T = win_turn(p, S, wave, k + 1);
+        bar.wait(S);
+        if (tid == 0) {
+            win_set(&S.freeq, qs + E);
+            win_set(&S.done, (int)k + 1);
+        }
     }
-    const WinBuf &P = buf[cur ^ 1];
-    for (int e = tid; e < pE; e += kWinThreads)
-        if (P.nxt[e] < 0) w[P.col[e]] = P.v[e];
+    // the last window's writes, after those of the one before it
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    bar.arrive(S);
+    bar.wait(S);
+#pragma unroll
+    for (int u = 0; u < kWinPer; ++u)
+        if (last_c[u] >= 0) p.w[last_c[u]] = last_v[u];
+}
+
+template <int LOSS, bool VAL>
+__global__ __launch_bounds__(kWinThreads) void k_stale_window(WinArgs p) {
+    __shared__ WinShared S;
+    if (threadIdx.x < kWinProd) S.staged[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        S.done = S.freeq = S.ackq = 0;
+        S.arrived = 0;
+    }
+    __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane(wave_in_block());
+    const int64_t nwin = cdiv_dev(p.n, p.W);
+    if (wave < kWinCons)
+        win_consume<LOSS, VAL>(p, S, wave, nwin);
+    else
+        win_produce<VAL>(p, S, wave - kWinCons, nwin);
 }
 
 // each feature's final value: the entry no later entry overwrites
@@ -408,17 +789,6 @@ int launch_stale(const pdb_csr *csr, const float *labels, int64_t n, float *w, f
     const int64_t timeout = opt.timeout;
     k_stale_ctrl_zero<<<1, 64, 0, s>>>(ws.ctrl);
     PDB_LAUNCHED();
-    if (nnz > 0) {
-        k_stale_clear<<<grid_for(nnz, kBlock, 8192), kBlock, 0, s>>>(ws.words, ws.overwritten,
-                                                                    ws.next, nnz);
-        PDB_LAUNCHED();
-        k_stale_sources<<<grid_for(n, kSWaves, 65536), kBlock, 0, s>>>(csr->row_ptr, n, prev,
-                                                                       delay, ws.rd,
-                                                                       ws.overwritten);
-        PDB_LAUNCHED();
-        k_stale_next<<<grid_for(nnz, kBlock, 8192), kBlock, 0, s>>>(prev, nnz, ws.next);
-        PDB_LAUNCHED();
-    }
     // windows of delay + 1 examples.  The windowed execution needs the
     // largest window to fit the block, and pays on chain-like inputs (most
     // examples share a feature with the one before: one block then beats a
@@ -443,11 +813,30 @@ int launch_stale(const pdb_csr *csr, const float *labels, int64_t n, float *w, f
         windowed = host.max_width <= kWinCap && (mode == PDB_STALE_WINDOWED || chain_like);
     }
     if (windowed) {
-        k_stale_window<LOSS, VAL><<<1, kWinThreads, 0, s>>>(csr->row_ptr, csr->col, csr->val,
-                                                            labels, w, prev, ws.rd, ws.next, n,
-                                                            nnz, W, lr);
+        // the words hold the entries' chains, the other arrays their places
+        // and where their values come from
+        int32_t *place = ws.overwritten, *from = ws.next;
+        if (nnz > 0) {
+            k_win_chains<<<grid_for(n, kSWaves, 65536), kBlock, 0, s>>>(csr->row_ptr, n, prev,
+                                                                        delay, W, ws.rd, ws.words);
+            k_win_places<<<grid_for(cdiv(n, W), 1, 65536), kBlock, 0, s>>>(csr->row_ptr, n, W,
+                                                                           ws.words, place);
+            k_win_from<<<grid_for(n, kSWaves, 65536), kBlock, 0, s>>>(csr->row_ptr, n, W, prev,
+                                                                      ws.rd, ws.words, from);
+            PDB_LAUNCHED();
+        }
+        const WinArgs p{csr->row_ptr, csr->col, csr->val, labels, w, place, from, n, nnz, W, lr};
+        k_stale_window<LOSS, VAL><<<1, kWinThreads, 0, s>>>(p);
         PDB_LAUNCHED();
         return PDB_OK;
+    }
+    if (nnz > 0) {
+        k_stale_clear<<<grid_for(nnz, kBlock, 8192), kBlock, 0, s>>>(ws.words, ws.overwritten, nnz);
+        PDB_LAUNCHED();
+        k_stale_sources<<<grid_for(n, kSWaves, 65536), kBlock, 0, s>>>(csr->row_ptr, n, prev,
+                                                                       delay, ws.rd,
+                                                                       ws.overwritten);
+        PDB_LAUNCHED();
     }
     // every block resident (a cooperative launch: the waves wait on each
     // other), at most one wave per example

@@ -155,3 +155,23 @@ def test_full_size_stale(gpu, cfg, delay):
     g = datagen.generate(cfg)
     lv, _ = gpu_schedule(native, gpu, g["row_ptr"], g["col"], g["d"], 0)
     check_stale(native, gpu, g, lv, delay)
+
+
+# Windows at the edges of the windowed execution's staging: 2048 examples and
+# 2048 entries in a window, entries beyond a producer's first loads (384),
+# rows of more than a wave's entries, chains of more than 8 links, the rings of
+# staged entries (4096) and values (8192) wrapping, and windows without entries.
+@pytest.mark.parametrize("n,lengths,d,delay", [
+    (6000, [1], 700, 2047), (300, [128], 128, 15), (260, [127, 128, 129, 1], 400, 15),
+    (900, [100], 150, 4), (3000, [20, 33, 40], 90, 50), (4000, [0, 0, 0, 3], 5, 1),
+    (3000, [0] * 40 + [200], 300, 7)])
+@pytest.mark.parametrize("loss,with_val", [(0, False), (1, True)])
+def test_window_staging_edges(gpu, n, lengths, d, delay, loss, with_val):
+    native = native_mod()
+    rng = np.random.default_rng(n + delay)
+    rows = [set(rng.choice(d, lengths[i % len(lengths)], replace=False).tolist()) for i in range(n)]
+    g = structured_problem(rows, loss, with_val, 3)
+    csr = native.Csr.from_numpy(g["row_ptr"], g["col"], None, gpu)
+    lv = native.Levels(g["n"], len(g["col"]), gpu)
+    native.pdb_schedule(csr, None, g["n"], g["d"], lv)
+    check_stale(native, gpu, g, lv, delay, opt=dict(stale_mode=2))
