@@ -125,11 +125,14 @@ hipError_t exclusive_scan_u32(const uint32_t *in, uint32_t *out, int64_t count, 
 // Stable LSD sort of (key, value) pairs on bits [lo_bit, bits) of the key.
 // vals_in == NULL means value = position.  Result in (*keys_out, *vals_out),
 // which is one of the two buffer pairs (the inputs themselves when
-// lo_bit >= bits; vals_in must then not be NULL).
+// lo_bit >= bits; vals_in must then not be NULL).  prev: the keys are entries in
+// feature order and vals_in their features; the pairs sorted are (entry, the
+// entry before it on its feature or 0xFFFFFFFF) (lo_bit < bits).
 hipError_t radix_sort_pairs(const uint32_t *keys_in, const uint32_t *vals_in, int64_t count,
                             int bits, uint32_t *kA, uint32_t *vA, uint32_t *kB, uint32_t *vB,
                             uint32_t *hist, uint32_t *scan_tmp, uint32_t **keys_out,
-                            uint32_t **vals_out, hipStream_t s, int lo_bit = 0);
+                            uint32_t **vals_out, hipStream_t s, int lo_bit = 0,
+                            bool prev = false);
 
 // ----------------------------------------------------------------------------
 // device helpers

@@ -113,40 +113,45 @@ __global__ __launch_bounds__(kBlock) void k_row_index(const int64_t *__restrict_
 
 // K2: previous writer of every entry from the feature-sorted order: pn[p] =
 // the entry just before p in p's feature list (its CSR index), -1 at a head.
-// K2 in two streaming passes instead of a scatter.  Scattered 4-byte stores
+// K2 in streaming passes instead of a scatter.  Scattered 4-byte stores
 // of prev_nz in entry order land one per 32-byte sector and wrote 8x the
-// array (config 3: 16 GB for 2 GB, 21 ms).  Here:
-//   1. k_prev_pairs: in feature order, each entry's previous entry on its
-//      feature (the entry before it in the sorted order, when it has the same
-//      feature) as an (entry, previous) pair, written in order; col_ptr and
-//      csc_row as before;
-//   2. the pairs sorted by entry index above its low kPlaceBits bits (the
-//      stable radix sort's passes on the high digits only);
-//   3. k_prev_place: entry indices are a permutation of 0 .. nnz-1, so block
+// array (500M Zipf entries: 16 GB for 2 GB, 21 ms).  Here:
+//   1. the (entry, previous entry) pairs, in feature order -- the previous
+//      entry is the one before it in the sorted order, when it has the same
+//      feature -- sorted by entry index above its low kPlaceBits bits (the
+//      stable radix sort's passes on the high digits only; the first pass
+//      forms the pairs as it reads, a pass over 16 bytes per entry less);
+//   2. k_prev_place: entry indices are a permutation of 0 .. nnz-1, so block
 //      b finds exactly the entries [b 2^kPlaceBits, (b+1) 2^kPlaceBits) at
 //      those positions of the sorted pairs; it places their previous entries
 //      in LDS and writes the range out in order.
 constexpr int kPlaceBits = 13;  // 8192 entries, 32 KB of LDS per block
 
-__global__ __launch_bounds__(kBlock) void k_prev_pairs(
-    const uint32_t *__restrict__ skeys, const uint32_t *__restrict__ svals, int64_t nnz,
-    int64_t d, const int32_t *__restrict__ row_idx, uint32_t *__restrict__ pk,
-    uint32_t *__restrict__ pv, int64_t *__restrict__ col_ptr, int32_t *__restrict__ csc_row) {
+// The pairs by themselves, for at most 2^kPlaceBits entries (no radix pass).
+__global__ __launch_bounds__(kBlock) void k_prev_pairs(const uint32_t *__restrict__ skeys,
+                                                       const uint32_t *__restrict__ svals,
+                                                       int64_t nnz, uint32_t *__restrict__ pk,
+                                                       uint32_t *__restrict__ pv) {
+    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < nnz;
+         q += (int64_t)gridDim.x * blockDim.x) {
+        pk[q] = svals[q];
+        pv[q] = (q == 0 || skeys[q - 1] != skeys[q]) ? 0xFFFFFFFFu : svals[q - 1];
+    }
+}
+
+// first position of every feature in the feature-sorted order
+__global__ __launch_bounds__(kBlock) void k_col_ptr(const uint32_t *__restrict__ skeys, int64_t nnz,
+                                                    int64_t d, int64_t *__restrict__ col_ptr) {
     for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < nnz;
          q += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t f = skeys[q];
-        const uint32_t p = svals[q];
-        const bool head = (q == 0) || skeys[q - 1] != f;
-        pk[q] = p;
-        pv[q] = head ? 0xFFFFFFFFu : svals[q - 1];
-        if (head) {
+        if (q == 0 || skeys[q - 1] != f) {
             const int64_t lo = (q == 0) ? 0 : (int64_t)skeys[q - 1] + 1;
             const int64_t hi = min((int64_t)f, d - 1);  // columns >= d: malformed input
             for (int64_t g = lo; g <= hi; ++g) col_ptr[g] = q;
         }
         if (q == nnz - 1)
             for (int64_t g = (int64_t)f + 1; g <= d; ++g) col_ptr[g] = nnz;
-        if (csc_row) csc_row[q] = row_idx[p];
     }
 }
 
@@ -184,6 +189,15 @@ __global__ __launch_bounds__(kBlock) void k_csc_row(const uint32_t *__restrict__
         csc_row[q] = row_idx[svals[q]];
 }
 
+// *p = max(*p, v), v > 0, by the wave's first lane.  Atomics to one address
+// go one after another, about 11 ns each (16,000 waves: 180 us), so a wave
+// whose value the address already holds or exceeds only reads it.
+template <class T>
+__device__ __forceinline__ void wave_atomic_max(T *p, T v) {
+    if (lane_id() == 0 && v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(p, v);
+}
+
 __global__ __launch_bounds__(kBlock) void k_max_diff(const int64_t *__restrict__ ptr,
                                                      int64_t count, Ctrl *ctrl) {
     long long m = 0;
@@ -192,7 +206,7 @@ __global__ __launch_bounds__(kBlock) void k_max_diff(const int64_t *__restrict__
         m = max(m, (long long)(ptr[i + 1] - ptr[i]));
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) m = max(m, (long long)__shfl_xor(m, off));
-    if (lane_id() == 0 && m > 0) atomicMax(&ctrl->max_width, m);
+    wave_atomic_max(&ctrl->max_width, m);
 }
 
 // ---- K3 chain-scan -------------------------------------------------------
@@ -886,7 +900,7 @@ __global__ __launch_bounds__(kBlock) void k_max_level(const int32_t *__restrict_
          i += (int64_t)gridDim.x * blockDim.x)
         m = max(m, level[i]);
     m = wave_max_i32(m);
-    if (lane_id() == 0 && m > 0) atomicMax(&ctrl->max_level, m);
+    wave_atomic_max(&ctrl->max_level, m);
 }
 
 // ---- K3 walk ---------------------------------------------------------------
@@ -1312,7 +1326,7 @@ __global__ __launch_bounds__(kBlock) void k_top_feature(const int64_t *__restric
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) best = max(best, (unsigned long long)__shfl_xor(best, off));
-    if (lane_id() == 0 && best > 0) atomicMax(&ctrl->top_feature, best);
+    wave_atomic_max(&ctrl->top_feature, best);
 }
 
 __global__ __launch_bounds__(kBlock) void k_spine_rows(const uint32_t *__restrict__ svals,
@@ -1625,6 +1639,9 @@ __global__ __launch_bounds__(kBlock) void k_chain_check(const int64_t *__restric
     const int lane = lane_id();
     const int64_t nw = (int64_t)gridDim.x * (kBlock / kWave);
     const int64_t enough = lim / 4 + 1;
+    __shared__ int s_breaks;
+    if (threadIdx.x == 0) s_breaks = 0;
+    __syncthreads();
     int breaks = 0, rows = 0;
     for (int64_t i = 1 + blockIdx.x * (int64_t)(kBlock / kWave) + wave_in_block(); i < lim; i += nw) {
         const int64_t lo = row_ptr[i - 1], b = row_ptr[i], e = row_ptr[i + 1];
@@ -1639,10 +1656,14 @@ __global__ __launch_bounds__(kBlock) void k_chain_check(const int64_t *__restric
             total = __builtin_amdgcn_readfirstlane(total);
             breaks = 0;
             rows = 0;
-            if (total >= enough) return;
+            if (total >= enough) break;
         }
     }
-    if (lane == 0 && breaks) atomicAdd(&ctrl->chain_breaks, breaks);
+    // the rest in one atomic per block: they go one after another (a wave
+    // each took 0.74 ms over a prefix of 65,536 rows that all break)
+    if (lane == 0 && breaks) atomicAdd(&s_breaks, breaks);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_breaks) atomicAdd(&ctrl->chain_breaks, s_breaks);
 }
 
 // Levels of a chain: every example conflicts with the one before it, so
@@ -1754,39 +1775,54 @@ int check_sizes(int64_t n, int64_t d, int64_t nnz) {
     return PDB_OK;
 }
 
-// K0 + K1 + K2 into the workspace: previous-writer entries into pn, col_ptr,
-// and csc_row when not null.
-int build_conflicts(const pdb_csr *csr, int64_t n, int64_t d, SchedWs &w, int32_t *pn,
-                    int64_t *col_ptr, int32_t *csc_row, const uint32_t **skeys_out,
-                    const uint32_t **svals_out, hipStream_t s) {
-    const int64_t nnz = csr->nnz;
+// K0: the row of every entry
+int build_rows(const pdb_csr *csr, int64_t n, const SchedWs &w, hipStream_t s) {
     if (n > 0) {
         k_row_index<<<grid_for(n, kBlock / kWave, 65536), kBlock, 0, s>>>(csr->row_ptr, n,
                                                                           w.row_idx);
         PDB_LAUNCHED();
     }
+    return PDB_OK;
+}
+
+// each feature's first position in the feature-sorted order
+int build_col_ptr(const uint32_t *sk, int64_t nnz, int64_t d, int64_t *col_ptr, hipStream_t s) {
+    if (nnz > 0)
+        k_col_ptr<<<grid_for(nnz, kBlock, 1 << 16), kBlock, 0, s>>>(sk, nnz, d, col_ptr);
+    else
+        k_fill_i64<<<grid_for(d + 1, kBlock, 4096), kBlock, 0, s>>>(col_ptr, d + 1, 0);
+    PDB_LAUNCHED();
+    return PDB_OK;
+}
+
+// K1 + K2 into the workspace: previous-writer entries into pn; the entries
+// sorted by feature in (*skeys_out, *svals_out).  The rows of the entries and
+// the features' positions are for the callers that need them (build_rows,
+// build_col_ptr): on a chain nobody does.
+int build_conflicts(const pdb_csr *csr, int64_t d, SchedWs &w, int32_t *pn,
+                    const uint32_t **skeys_out, const uint32_t **svals_out, hipStream_t s) {
+    const int64_t nnz = csr->nnz;
     uint32_t *sk = nullptr, *sv = nullptr;
     const int bits = bit_length(d > 1 ? (uint64_t)(d - 1) : 1);
     PDB_HIP(radix_sort_pairs(reinterpret_cast<const uint32_t *>(csr->col), nullptr, nnz, bits,
                              w.kA, w.vA, w.kB, w.vB, w.hist, w.scan_tmp, &sk, &sv, s));
     if (nnz > 0) {
-        // the radix pair not holding the sorted entries takes the pairs; the
-        // sort's other buffers are the candidates array and pn itself
+        // the sort's buffers: the candidates array and pn, and the radix pair
+        // not holding the sorted entries
         uint32_t *fk = (sk == w.kA) ? w.kB : w.kA;
         uint32_t *fv = (sv == w.vA) ? w.vB : w.vA;
-        k_prev_pairs<<<grid_for(nnz, kBlock, 1 << 16), kBlock, 0, s>>>(
-            sk, sv, nnz, d, w.row_idx, fk, fv, col_ptr, csc_row);
-        PDB_LAUNCHED();
-        uint32_t *ok = nullptr, *ov = nullptr;
-        PDB_HIP(radix_sort_pairs(fk, fv, nnz, bit_length((uint64_t)(nnz > 1 ? nnz - 1 : 1)),
-                                 reinterpret_cast<uint32_t *>(w.cand),
-                                 reinterpret_cast<uint32_t *>(pn), fk, fv, w.hist, w.scan_tmp,
-                                 &ok, &ov, s, kPlaceBits));
+        uint32_t *ok = fk, *ov = fv;
+        const int ebits = bit_length((uint64_t)(nnz > 1 ? nnz - 1 : 1));
+        if (ebits > kPlaceBits) {
+            PDB_HIP(radix_sort_pairs(sv, sk, nnz, ebits, reinterpret_cast<uint32_t *>(w.cand),
+                                     reinterpret_cast<uint32_t *>(pn), fk, fv, w.hist, w.scan_tmp,
+                                     &ok, &ov, s, kPlaceBits, true));
+        } else {
+            k_prev_pairs<<<grid_for(nnz, kBlock, 1 << 16), kBlock, 0, s>>>(sk, sv, nnz, fk, fv);
+            PDB_LAUNCHED();
+        }
         k_prev_place<<<(unsigned)cdiv(nnz, (int64_t)1 << kPlaceBits), kBlock, 0, s>>>(ok, ov, nnz,
                                                                                       pn);
-        PDB_LAUNCHED();
-    } else {
-        k_fill_i64<<<grid_for(d + 1, kBlock, 4096), kBlock, 0, s>>>(col_ptr, d + 1, 0);
         PDB_LAUNCHED();
     }
     *skeys_out = sk;
@@ -1858,8 +1894,15 @@ extern "C" int pdb_transpose(const pdb_csr *csr, int64_t n, int64_t d, int64_t *
     if (rc != PDB_OK) return rc;
     if (!col_ptr || (csr->nnz > 0 && !csc_row)) return PDB_ERR_INVALID_ARG;
     const uint32_t *sk, *sv;
-    rc = build_conflicts(csr, n, d, w, w.pn, col_ptr, csc_row, &sk, &sv, stream);
+    rc = build_rows(csr, n, w, stream);
+    if (rc == PDB_OK) rc = build_conflicts(csr, d, w, w.pn, &sk, &sv, stream);
+    if (rc == PDB_OK) rc = build_col_ptr(sk, csr->nnz, d, col_ptr, stream);
     if (rc != PDB_OK) return rc;
+    if (csr->nnz > 0) {
+        k_csc_row<<<grid_for(csr->nnz, kBlock, 1 << 16), kBlock, 0, stream>>>(sv, csr->nnz,
+                                                                             w.row_idx, csc_row);
+        PDB_LAUNCHED();
+    }
     PDB_HIP(hipStreamSynchronize(stream));
     return PDB_OK;
 }
@@ -1872,7 +1915,8 @@ extern "C" int pdb_prev_writer(const pdb_csr *csr, int64_t n, int64_t d, int32_t
     if (csr->nnz > 0 && !prev_row) return PDB_ERR_INVALID_ARG;
     int32_t *pn = prev_nz ? prev_nz : w.pn;
     const uint32_t *sk, *sv;
-    rc = build_conflicts(csr, n, d, w, pn, w.col_ptr, nullptr, &sk, &sv, stream);
+    rc = build_rows(csr, n, w, stream);
+    if (rc == PDB_OK) rc = build_conflicts(csr, d, w, pn, &sk, &sv, stream);
     if (rc != PDB_OK) return rc;
     if (csr->nnz > 0) {
         k_prev_row<<<grid_for(csr->nnz, kBlock, 1 << 16), kBlock, 0, stream>>>(pn, csr->nnz,
@@ -1911,10 +1955,10 @@ extern "C" int pdb_schedule(const pdb_csr *csr, const float *labels, int64_t n, 
         return PDB_OK;
     }
 
-    // K0-K2
+    // K1, K2 (K0 and col_ptr follow unless the input is a chain)
     int32_t *pn = lv->prev_nz ? lv->prev_nz : w.pn;
     const uint32_t *sk, *sv;
-    rc = build_conflicts(csr, n, d, w, pn, w.col_ptr, nullptr, &sk, &sv, s);
+    rc = build_conflicts(csr, d, w, pn, &sk, &sv, s);
     if (rc != PDB_OK) return rc;
     // the radix buffer pair that does not hold the sorted entries is free
     int32_t *free_k = reinterpret_cast<int32_t *>((sk == w.kA) ? w.kB : w.kA);
@@ -1929,8 +1973,8 @@ extern "C" int pdb_schedule(const pdb_csr *csr, const float *labels, int64_t n, 
         // the input is no chain and is taken as not chain-like without
         // reading the rest (every method is exact; this only picks one)
         const int64_t lim0 = std::min<int64_t>(n, kChainPrefix);
-        k_chain_check<<<grid_for(lim0, kBlock / kWave, 65536), kBlock, 0, s>>>(csr->row_ptr, lim0,
-                                                                               pn, w.ctrl);
+        k_chain_check<<<grid_for(lim0, kBlock / kWave, 2048), kBlock, 0, s>>>(csr->row_ptr, lim0,
+                                                                              pn, w.ctrl);
         PDB_LAUNCHED();
         rc = read_ctrl(w.ctrl, &host, s);
         if (rc != PDB_OK) return rc;
@@ -1958,13 +2002,23 @@ extern "C" int pdb_schedule(const pdb_csr *csr, const float *labels, int64_t n, 
         chain_like = !prefix_breaks && 4 * (int64_t)host.chain_breaks <= n;
     }
 
+    rc = build_rows(csr, n, w, s);
+    if (rc != PDB_OK) return rc;
+
     // which method: the spine when the most frequent feature misses at most
     // kSpineMaxE rows, else the walk on chain-like inputs, else dataflow
     int use = method;
     int rounds = 0;
     int64_t top_count = 0, top_f = 0;
-    if (method == PDB_SCHED_AUTO || method == PDB_SCHED_SPINE) {
-        k_top_feature<<<grid_for(d, kBlock, 4096), kBlock, 0, s>>>(w.col_ptr, d, w.ctrl);
+    // a row and the row before it that both hold a feature do not break the
+    // chain, so a feature that misses m rows allows at most 2 m breaks: beyond
+    // that the spine cannot apply, and the features need not be counted
+    if (method == PDB_SCHED_AUTO && (int64_t)host.chain_breaks > 2 * (int64_t)kSpineMaxE) {
+        use = chain_like ? PDB_SCHED_WALK : PDB_SCHED_DATAFLOW;
+    } else if (method == PDB_SCHED_AUTO || method == PDB_SCHED_SPINE) {
+        rc = build_col_ptr(sk, nnz, d, w.col_ptr, s);
+        if (rc != PDB_OK) return rc;
+        k_top_feature<<<grid_for(d, kBlock, 256), kBlock, 0, s>>>(w.col_ptr, d, w.ctrl);
         PDB_LAUNCHED();
         rc = read_ctrl(w.ctrl, &host, s);
         if (rc != PDB_OK) return rc;
@@ -1979,7 +2033,7 @@ extern "C" int pdb_schedule(const pdb_csr *csr, const float *labels, int64_t n, 
     // would run: the short-row walk
     if ((method == PDB_SCHED_AUTO && use == PDB_SCHED_DATAFLOW) || method == PDB_SCHED_SHORT) {
         k_fill_i32<<<1, 64, 0, s>>>(reinterpret_cast<int32_t *>(&w.ctrl->max_width), 2, 0);
-        k_max_diff<<<grid_for(n, kBlock, 4096), kBlock, 0, s>>>(csr->row_ptr, n, w.ctrl);
+        k_max_diff<<<grid_for(n, kBlock, 256), kBlock, 0, s>>>(csr->row_ptr, n, w.ctrl);
         PDB_LAUNCHED();
         rc = read_ctrl(w.ctrl, &host, s);
         if (rc != PDB_OK) return rc;
@@ -2165,7 +2219,7 @@ extern "C" int pdb_schedule(const pdb_csr *csr, const float *labels, int64_t n, 
     }
 
     // L, then K4
-    k_max_level<<<grid_for(n, kBlock, 4096), kBlock, 0, s>>>(lv->level, n, w.ctrl);
+    k_max_level<<<grid_for(n, kBlock, 256), kBlock, 0, s>>>(lv->level, n, w.ctrl);
     PDB_LAUNCHED();
     rc = read_ctrl(w.ctrl, &host, s);
     if (rc != PDB_OK) return rc;
@@ -2182,7 +2236,7 @@ extern "C" int pdb_schedule(const pdb_csr *csr, const float *labels, int64_t n, 
                                                               lv->perm, lv->n_levels);
     k_fill_i32<<<1, 64, 0, s>>>(reinterpret_cast<int32_t *>(&w.ctrl->max_width), 2, 0);
     PDB_LAUNCHED();
-    k_max_diff<<<grid_for(L, kBlock, 4096), kBlock, 0, s>>>(lv->level_ptr, L, w.ctrl);
+    k_max_diff<<<grid_for(L, kBlock, 256), kBlock, 0, s>>>(lv->level_ptr, L, w.ctrl);
     PDB_LAUNCHED();
     rc = read_ctrl(w.ctrl, &host, s);
     if (rc != PDB_OK) return rc;
@@ -2216,7 +2270,8 @@ extern "C" int pdb_validate_schedule(const pdb_csr *csr, int64_t n, int64_t d,
     PDB_LAUNCHED();
     // previous writers from the CSR itself (nothing of the schedule is used)
     const uint32_t *sk, *sv;
-    rc = build_conflicts(csr, n, d, w, w.pn, w.col_ptr, nullptr, &sk, &sv, s);
+    rc = build_rows(csr, n, w, s);
+    if (rc == PDB_OK) rc = build_conflicts(csr, d, w, w.pn, &sk, &sv, s);
     if (rc != PDB_OK) return rc;
     // the radix buffer pair that does not hold the sorted entries is free
     uint32_t *seen = (sk == w.kA) ? w.kB : w.kA;
