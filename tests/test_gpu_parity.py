@@ -703,3 +703,18 @@ def test_pipeline_select_free_guard(gpu, case, fast):
     if case in ("plain", "valued", "negzero", "squares"):
         ref = oracle.sgd_epoch(row_ptr, col, val, y, w0, lr, loss, oracle.MATCHED)
         assert np.array_equal(w.cpu().numpy().view(np.int32), ref.view(np.int32))
+
+
+# The walk's windows of many short runs (more than one per 24 rows) push levels
+# 64 rows at a time: runs on both sides of that line, of a sub-chunk's length and
+# around it, windows that end inside a sub-chunk, and rows that write for most
+# of their 64 or for none.
+@pytest.mark.parametrize("run_len", [1, 2, 9, 23, 24, 25, 63, 64, 65])
+@pytest.mark.parametrize("extra,d", [(0, 1), (3, 40), (9, 900)])
+def test_walk_pushed_levels(gpu, run_len, extra, d):
+    native = native_mod()
+    rng = np.random.default_rng(run_len + 100 * extra)
+    n = 1700
+    rows = [{d + i // run_len} | set(rng.integers(0, d, extra).tolist()) for i in range(n)]
+    row_ptr, col = csr_from_rows(rows)
+    check_schedule(native, gpu, row_ptr, col, int(col.max()) + 1, native.PDB_SCHED_WALK)
