@@ -19,6 +19,12 @@
 // weight once.  Levels run one after another: a level wider than `thin` is
 // spread over the grid followed by a device-wide barrier, runs of narrow
 // levels go to block 0 with block barriers between batches.
+//
+// Sync-free epoch (no levels): blocks take batches in index order, and each
+// weight and the union entry that last wrote it share a 64-bit word.  A batch
+// waits for the words of its union, then runs the two phases
+// (k_batch_syncfree); or, where few entries share their feature with another
+// of the batch, its examples wait each for its own words (k_batch_flow).
 #include <climits>
 
 #include "pdb_math.h"
@@ -636,9 +642,11 @@ __device__ bool fast_batch(const BatchOp<LOSS, VAL> &op, const int32_t *uprev,
         if (m > kWave) {
             const float a1 = Sh.uw[at[2 * j + 1] & 0xFFFF];
             if (kWave + lane < m) acc[j] = __builtin_fmaf(a1, VAL ? x[2 * j + 1] : 1.0f, acc[j]);
-            for (int k = 2 * kWave + lane; k < m; k += kWave)
-                acc[j] = __builtin_fmaf(Sh.uw[Sh.eu[first(j) + k] & 0xFFFF],
-                                        VAL ? op.val[pb + first(j) + k] : 1.0f, acc[j]);
+            for (int k = 2 * kWave + lane; k < m; k += kWave) {
+                const int e = Sh.eu[first(j) + k];
+                acc[j] = __builtin_fmaf(Sh.uw[e & 0xFFFF], VAL ? Sh.ox[(unsigned)e >> 16] : 1.0f,
+                                        acc[j]);
+            }
         }
     }
 #pragma unroll
@@ -680,12 +688,45 @@ __device__ bool fast_batch(const BatchOp<LOSS, VAL> &op, const int32_t *uprev,
     return true;
 }
 
+// Batches that cannot run example by example (k_batch_flow), counted: a wave
+// per batch.
+__global__ __launch_bounds__(kBlock) void k_batch_whole(const int64_t *__restrict__ row_ptr,
+                                                        int64_t n, int64_t B, int64_t nb,
+                                                        Ctrl *ctrl) {
+    __shared__ int s_count;
+    if (threadIdx.x == 0) s_count = 0;
+    __syncthreads();
+    const int64_t nw = (int64_t)gridDim.x * (kBlock / kWave);
+    int count = 0;
+    for (int64_t b = (blockIdx.x * (int64_t)kBlock + threadIdx.x) / kWave; b < nb; b += nw) {
+        const int64_t i0 = b * B, i1 = min(i0 + B, n);
+        bool over = row_ptr[i1] - row_ptr[i0] > kFlowCap;
+        for (int64_t i = i0 + lane_id(); i < i1; i += kWave)
+            over |= row_ptr[i + 1] - row_ptr[i] > 2 * kWave;
+        count += __ballot(over) != 0;
+    }
+    if (lane_id() == 0 && count) atomicAdd(&s_count, count);
+    __syncthreads();
+    if (threadIdx.x == 0 && s_count) atomicAdd(&ctrl->whole_batches, s_count);
+}
+
+// At most one batch in four does not fit k_batch_flow, which runs such a
+// batch as a whole too, but without fast_batch, whose registers would cost
+// every batch (8.9 -> 11.0 ms for 5,000 batches of 100): 100,000 examples of
+// 100-180 uniform features, batches of 50, none of which fits, take 22.9 ms in
+// k_batch_syncfree and 47.9 ms there.  With 19% of the batches too long
+// (200,000 examples of about 100 features, batches of 64) it is 36.0 and 17.6 ms.
+__device__ __forceinline__ bool by_example(const Ctrl *ctrl, int64_t nb) {
+    return 4 * (int64_t)ctrl->whole_batches <= nb;
+}
+
 template <int LOSS, bool VAL>
 __global__ __launch_bounds__(kBB) void k_batch_syncfree(BatchOp<LOSS, VAL> op,
                                                        const int32_t *__restrict__ uprev,
                                                        unsigned long long *bw, int64_t nb,
-                                                       Ctrl *ctrl, int64_t timeout) {
+                                                       bool flow, Ctrl *ctrl, int64_t timeout) {
     __shared__ SfShared Sh;
+    if (flow && by_example(ctrl, nb)) return;
     for (;;) {
         if (threadIdx.x == 0) {
             Sh.ticket = (int64_t)atomicAdd(&ctrl->ticket, 1ull);
@@ -1104,6 +1145,7 @@ __global__ __launch_bounds__(kBB) void k_batch_flow(BatchOp<LOSS, VAL> op,
     } Sh;
     __shared__ int64_t s_ticket;
     __shared__ int s_long;
+    if (!by_example(ctrl, nb)) return;
     for (;;) {
         if (threadIdx.x == 0) {
             s_ticket = (int64_t)atomicAdd(&ctrl->ticket, 1ull);
@@ -1210,16 +1252,23 @@ int launch_batch_syncfree(const BatchOp<LOSS, VAL> &op, const pdb_levels *lv, in
     // of 8 4.4 and 2.3 ms).  It addresses words with 32-bit byte offsets.
     const bool flow = U > 0 && 32 * (nnz - U) <= nnz && op.B >= 8 && op.B <= kFlowB &&
                       d <= int64_t(1) << 28;
-    // the most examples per worker that a batch needs, so that they are all in
-    // flight together: with half as many, batches of 128 took 50 ms, not 15.7
-    if (!flow)
-        k_batch_syncfree<LOSS, VAL><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, ctrl, timeout);
-    else if (op.B <= kFlowWorkers * kFlowG)
-        k_batch_flow<LOSS, VAL, kFlowG><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, ctrl,
-                                                             timeout);
-    else
-        k_batch_flow<LOSS, VAL, 2 * kFlowG><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, ctrl,
+    if (flow) {
+        // what a batch holds is on the device: both kernels are launched, and
+        // one of them returns at once (5 us)
+        k_batch_whole<<<grid_for(nb, kBlock / kWave, 1024), kBlock, 0, s>>>(op.row_ptr, op.n, op.B,
+                                                                           nb, ctrl);
+        PDB_LAUNCHED();
+        // the most examples per worker that a batch needs, so that they are all in
+        // flight together: with half as many, batches of 128 took 50 ms, not 15.7
+        if (op.B <= kFlowWorkers * kFlowG)
+            k_batch_flow<LOSS, VAL, kFlowG><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, ctrl,
                                                                  timeout);
+        else
+            k_batch_flow<LOSS, VAL, 2 * kFlowG><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb,
+                                                                     ctrl, timeout);
+        PDB_LAUNCHED();
+    }
+    k_batch_syncfree<LOSS, VAL><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, flow, ctrl, timeout);
     PDB_LAUNCHED();
     if (d > 0) {
         k_bw_out<<<grid_for(d, kBlock, 8192), kBlock, 0, s>>>(bw, op.w, d);

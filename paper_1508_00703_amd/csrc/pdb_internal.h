@@ -56,7 +56,7 @@ struct Ctrl {
     int changed;    // chain-scan: some level increased in this round
     int bad;        // validation failure flag
     int max_level;  // reductions read back by the host
-    int pad0;
+    int whole_batches;  // sync-free mini-batches: batches that cannot run by example
     unsigned long long ticket;  // work ticket for dataflow kernels
     long long max_width;
     // width-1 pipeline counters (clock cycles of the consumer wave): total,

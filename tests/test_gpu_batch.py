@@ -220,9 +220,11 @@ def test_full_size_batch_levels(gpu, cfg):
 # shares its feature with another of its batch) run example by example.  Edges:
 # examples per worker and per block (104, 208, 256), entries per example (0,
 # 64, 128) and per batch (16384), entries on shared features of one batch
-# (4096); beyond the last four a batch runs by itself as a whole.
+# (4096); beyond the last four a batch runs by itself as a whole, and every
+# batch does when more than a quarter of them hold a longer example.
 @pytest.mark.parametrize("B,extra", [(8, ""), (13, ""), (104, ""), (105, ""), (208, ""),
-                                     (209, ""), (256, "big"), (100, "long"), (100, "shared")])
+                                     (209, ""), (256, "big"), (100, "long"), (100, "shared"),
+                                     (8, "few long"), (100, "all long")])
 @pytest.mark.parametrize("loss,with_val", [(0, False), (1, True)])
 def test_batches_example_by_example(gpu, B, extra, loss, with_val):
     native = native_mod()
@@ -231,7 +233,12 @@ def test_batches_example_by_example(gpu, B, extra, loss, with_val):
     n, d = 1800, 600_000
     lengths = rng.choice([0, 1, 5, 63, 64, 65, 100, 127, 128], n)
     if extra == "big":
-        lengths[256:512] = 70  # 17920 entries in the second batch
+        lengths = np.minimum(lengths, 100)
+        lengths[256:512] = 70  # 17920 entries in the second batch, fewer in the others
+    if extra == "all long":
+        lengths[::B] = 129  # in every batch: none runs example by example
+    if extra == "few long":
+        lengths[: n // 5 : B] = 129  # in a fifth of the batches
     rows = [set(sample(range(d), int(m))) for m in lengths]
     if extra == "long":
         rows[350] = set(sample(range(d), 129))
