@@ -19,7 +19,8 @@
 // feature's writes through the window in example order.  Chosen when a
 // window's entries fit the block's LDS.  Passes over all windows before it lay
 // every window's entries out by feature, in example order (an entry's place),
-// so that a feature's chain is a stretch of consecutive places.
+// so that a feature's chain is a stretch of consecutive places.  (Wide
+// windows are staged and run by all waves together, without those passes.)
 //
 // Sync-free (otherwise): every stored entry owns a 64-bit word (the value it
 // wrote, its own index as the tag); waves take examples in index order; an
@@ -38,15 +39,18 @@ namespace {
 
 constexpr int kSWaves = kBlock / kWave;
 constexpr int kWinCap = 2048;          // entries (and examples) of a window held in LDS
+constexpr int kWinWide = kWinCap * 3 / 4;  // wider windows: k_stale_wide
 constexpr int kWinThreads = 1024;
 constexpr int kWinWaves = kWinThreads / kWave;
 
 struct StaleWs {
     Ctrl *ctrl;
-    unsigned long long *words;  // [nnz]
+    unsigned long long *words;  // [nnz] sync-free: (value, entry); windowed: chain
     int32_t *rd;                // [nnz] read source, -1 = the initial weight
-    int32_t *overwritten;       // [nnz] 1 when a later entry writes the same feature
-    int32_t *next;              // [nnz] next entry on the same feature, -1 = none
+    int32_t *overwritten;       // [nnz] sync-free: 1 when a later entry writes the same
+                                // feature; windowed: the entry's place in its window
+    int32_t *next;              // [nnz] windowed: where the entry's read is taken from, or in
+                                // wide windows the next entry on the feature, -1 = none
     size_t total;
 };
 
@@ -772,6 +776,193 @@ __global__ __launch_bounds__(kWinThreads) void k_stale_window(WinArgs p) {
         win_produce<VAL>(p, S, wave - kWinCons, nwin);
 }
 
+constexpr int kWidePer = kWinCap / kWinThreads;  // entries per thread
+
+__global__ void k_stale_no_next(int32_t *__restrict__ next, int64_t nnz) {
+    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < nnz;
+         q += (int64_t)gridDim.x * blockDim.x)
+        next[q] = -1;
+}
+
+// next writer: the entry whose previous entry on the feature is q
+__global__ void k_stale_next(const int32_t *__restrict__ prev, int64_t nnz,
+                             int32_t *__restrict__ next) {
+    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < nnz;
+         q += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t p = prev[q];
+        if (p >= 0) next[p] = (int32_t)q;
+    }
+}
+
+// The windowed execution where windows are large, one block of kWinThreads
+// threads that all load, stage and compute.  Thread t handles entries t and
+// t + kWinThreads of every window, and examples t and t + kWinThreads.  What
+// a window reads from memory that earlier windows do
+// not change (columns, values, read sources, previous and next writers, row
+// bounds, labels) is loaded two windows ahead into registers; the weights it
+// reads from w are loaded one window ahead, right after the commit that
+// makes w the state they need.
+struct WideBuf {
+    int32_t col[kWinCap];
+    float x[kWinCap];
+    float rv[kWinCap];     // the value the entry reads
+    float v[kWinCap];      // the value the entry writes
+    int32_t nxt[kWinCap];  // next entry on the feature (CSR index), -1 = none
+    int16_t ex[kWinCap];   // the entry's example within the window
+    int32_t rp[kWinCap + 1];  // example bounds, relative to the window's first entry
+    float y[kWinCap];
+};
+
+// a window's loads, per thread
+struct WideMeta {
+    int32_t col[kWidePer], rd[kWidePer], pv[kWidePer], nx[kWidePer];
+    float x[kWidePer];
+    int64_t rp[kWidePer + 1];  // row_ptr of examples t, t + kWinThreads (and the end)
+    float y[kWidePer];
+};
+
+template <bool VAL>
+__device__ __forceinline__ void wide_load(WideMeta &m, int64_t k, int64_t nwin, int64_t W,
+                                         int64_t n, int64_t nnz, int64_t q0,
+                                         const int64_t *__restrict__ row_ptr,
+                                         const int32_t *__restrict__ col,
+                                         const float *__restrict__ val,
+                                         const float *__restrict__ y,
+                                         const int32_t *__restrict__ prev,
+                                         const int32_t *__restrict__ rd,
+                                         const int32_t *__restrict__ next) {
+    if (k >= nwin) return;
+    const int tid = threadIdx.x;
+    const int64_t a0 = k * W, a1 = min(n, a0 + W);
+#pragma unroll
+    for (int u = 0; u < kWidePer; ++u) {
+        // entries past the window's end are loaded (clamped) and ignored
+        const int64_t q = min(q0 + tid + u * kWinThreads, nnz - 1);
+        if (nnz > 0) {
+            m.col[u] = col[q];
+            m.rd[u] = rd[q];
+            m.pv[u] = prev[q];
+            m.nx[u] = next[q];
+            m.x[u] = VAL ? val[q] : 1.0f;
+        }
+        const int64_t a = min(a0 + tid + u * kWinThreads, a1);
+        m.rp[u] = row_ptr[a];
+        m.y[u] = y[min(a, n - 1)];
+    }
+    m.rp[kWidePer] = row_ptr[min(a0 + tid + kWidePer * kWinThreads, a1)];
+}
+
+template <int LOSS, bool VAL>
+__global__ __launch_bounds__(kWinThreads) void k_stale_wide(
+    const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
+    const float *__restrict__ val, const float *__restrict__ y, float *w,
+    const int32_t *__restrict__ prev, const int32_t *__restrict__ rd,
+    const int32_t *__restrict__ next, int64_t n, int64_t nnz, int64_t W, float lr) {
+    __shared__ WideBuf buf[2];
+    __shared__ float S[kWinCap];
+    const int tid = threadIdx.x, lane = lane_id(), wave = wave_in_block();
+    const int64_t nwin = cdiv_dev(n, W);
+    auto qstart = [&](int64_t k) { return row_ptr[min(n, k * W)]; };
+    WideMeta m0, m1, m2;
+    int64_t q0 = qstart(0), q1 = qstart(1), q2 = qstart(2);
+    wide_load<VAL>(m0, 0, nwin, W, n, nnz, q0, row_ptr, col, val, y, prev, rd, next);
+    wide_load<VAL>(m1, 1, nwin, W, n, nnz, q1, row_ptr, col, val, y, prev, rd, next);
+    float wv[kWidePer];
+#pragma unroll
+    for (int u = 0; u < kWidePer; ++u) wv[u] = (nnz > 0) ? w[m0.col[u]] : 0.0f;
+    int cur = 0;
+    int64_t pq0 = 0;  // first entry of the previous window (its end is the current start)
+    int pE = 0;       // entries of the previous window
+    // One window.  mc, mn, mnn: the loads of windows k, k + 1, k + 2 (mnn is
+    // issued here); qa, qb, qc: the first entries of windows k, k + 1, k + 2
+    // (qa receives that of window k + 3).  The three calls per loop
+    // iteration rotate the roles, so no register copy waits on a load still
+    // in flight.
+    auto window = [&](int64_t k, WideMeta &mc, WideMeta &mn, WideMeta &mnn, int64_t &qa,
+                      int64_t qb, int64_t qc) {
+        const int64_t a0 = k * W, a1 = min(n, a0 + W);
+        const int64_t qs = qa;
+        const int E = (int)(qb - qs), nex = (int)(a1 - a0);
+        WideBuf &C = buf[cur];
+        const WideBuf &P = buf[cur ^ 1];
+        // window k into LDS; reads from window k - 1's writes, else from w
+        // as it was before window k - 1
+#pragma unroll
+        for (int u = 0; u < kWidePer; ++u) {
+            const int e = tid + u * kWinThreads;
+            if (e < E) {
+                const int32_t r = mc.rd[u];
+                C.col[e] = mc.col[u];
+                C.x[e] = mc.x[u];
+                C.nxt[e] = mc.nx[u];
+                C.rv[e] = (r >= pq0) ? P.v[r - pq0] : wv[u];
+            }
+            if (e <= nex) C.rp[e] = (int32_t)(mc.rp[u] - qs);
+            if (e < nex) C.y[e] = mc.y[u];
+        }
+        if (tid + kWidePer * kWinThreads <= nex)
+            C.rp[tid + kWidePer * kWinThreads] = (int32_t)(mc.rp[kWidePer] - qs);
+        __syncthreads();
+        // commit window k - 1: the last write of each feature it touched
+        for (int e = tid; e < pE; e += kWinThreads) {
+            const int32_t nx = P.nxt[e];
+            if (nx < 0 || nx >= qs) w[P.col[e]] = P.v[e];
+        }
+        // window k + 2's loads, in flight while this window computes
+        wide_load<VAL>(mnn, k + 2, nwin, W, n, nnz, qc, row_ptr, col, val, y, prev, rd, next);
+        qa = qstart(k + 3);
+        // steps, a wave per example, dot products in the matched order
+        for (int j = wave; j < nex; j += kWinWaves) {
+            const int b = C.rp[j], mm = C.rp[j + 1] - b;
+            float acc = 0.0f;
+            for (int t = lane; t < mm; t += kWave) {
+                acc = __builtin_fmaf(C.rv[b + t], C.x[b + t], acc);
+                C.ex[b + t] = (int16_t)j;
+            }
+            const float z = wave_sum64(acc);
+            if (lane == 0) S[j] = sgd_scale<LOSS>(z, C.y[j], lr);
+        }
+        __syncthreads();
+        // window k + 1's reads of w: w is now the state before window k
+        if (k + 1 < nwin && nnz > 0) {
+#pragma unroll
+            for (int u = 0; u < kWidePer; ++u) wv[u] = w[mn.col[u]];
+        }
+        // writes: each feature's entries of the window in example order,
+        // from the value its previous writer left
+#pragma unroll
+        for (int u = 0; u < kWidePer; ++u) {
+            const int e = tid + u * kWinThreads;
+            const int32_t pv = mc.pv[u];
+            if (e < E && pv < qs) {
+                float v = (pv >= pq0) ? P.v[pv - pq0] : C.rv[e];
+                int ee = e;
+                for (;;) {
+                    v = __builtin_fmaf(-S[C.ex[ee]], C.x[ee], v);
+                    C.v[ee] = v;
+                    const int32_t nx = C.nxt[ee];
+                    if (nx < 0 || nx >= qb) break;
+                    ee = (int)(nx - qs);
+                }
+            }
+        }
+        __syncthreads();
+        pq0 = qs;
+        pE = E;
+        cur ^= 1;
+    };
+    for (int64_t k = 0; k < nwin; k += 3) {
+        window(k, m0, m1, m2, q0, q1, q2);
+        if (k + 1 >= nwin) break;
+        window(k + 1, m1, m2, m0, q1, q2, q0);
+        if (k + 2 >= nwin) break;
+        window(k + 2, m2, m0, m1, q2, q0, q1);
+    }
+    const WideBuf &P = buf[cur ^ 1];
+    for (int e = tid; e < pE; e += kWinThreads)
+        if (P.nxt[e] < 0) w[P.col[e]] = P.v[e];
+}
+
 // each feature's final value: the entry no later entry overwrites
 __global__ __launch_bounds__(kBlock) void k_stale_final(const int32_t *__restrict__ col,
                                                         const unsigned long long *__restrict__ words,
@@ -797,6 +988,7 @@ int launch_stale(const pdb_csr *csr, const float *labels, int64_t n, float *w, f
     const int mode = opt.stale_mode;
     const int64_t W = delay >= n ? std::max<int64_t>(n, 1) : delay + 1;  // no overflow at huge delays
     bool windowed = false;
+    int64_t widest = 0;
     if (mode != PDB_STALE_SYNCFREE && W <= kWinCap) {
         k_window_max<<<grid_for(cdiv(n, W), kBlock, 4096), kBlock, 0, s>>>(csr->row_ptr, n, W,
                                                                            ws.ctrl);
@@ -810,7 +1002,25 @@ int launch_stale(const pdb_csr *csr, const float *labels, int64_t n, float *w, f
         PDB_HIP(hipMemcpyAsync(&host, ws.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
         PDB_HIP(hipStreamSynchronize(s));
         const bool chain_like = 4 * (int64_t)host.chain_breaks <= n;
+        widest = host.max_width;
         windowed = host.max_width <= kWinCap && (mode == PDB_STALE_WINDOWED || chain_like);
+    }
+    // Windows of more than kWinWide entries: the producers' buffers hold fewer
+    // than three, so at most two producers load at a time and the chain waits
+    // for them (valued Zipf-1.2 features: 5 x 200-400 58.9 ms that way, 32.9
+    // here; 31 x 50 9.7 and 8.8; below the line 9 x 100-180, the widest 1.5K
+    // entries, 15.2 and 17.1).
+    if (windowed && widest > kWinWide) {
+        k_stale_no_next<<<grid_for(nnz, kBlock, 8192), kBlock, 0, s>>>(ws.next, nnz);
+        k_stale_sources<<<grid_for(n, kSWaves, 65536), kBlock, 0, s>>>(csr->row_ptr, n, prev,
+                                                                       delay, ws.rd,
+                                                                       ws.overwritten);
+        k_stale_next<<<grid_for(nnz, kBlock, 8192), kBlock, 0, s>>>(prev, nnz, ws.next);
+        PDB_LAUNCHED();
+        k_stale_wide<LOSS, VAL><<<1, kWinThreads, 0, s>>>(csr->row_ptr, csr->col, csr->val, labels,
+                                                          w, prev, ws.rd, ws.next, n, nnz, W, lr);
+        PDB_LAUNCHED();
+        return PDB_OK;
     }
     if (windowed) {
         // the words hold the entries' chains, the other arrays their places

@@ -157,14 +157,16 @@ def test_full_size_stale(gpu, cfg, delay):
     check_stale(native, gpu, g, lv, delay)
 
 
-# Windows at the edges of the windowed execution's staging: 2048 examples and
-# 2048 entries in a window, entries beyond a producer's first loads (384),
+# Windows at the edges of the windowed executions: 1536 entries in the widest
+# (producers stage them) and more (every wave does), 2048 examples and 2048
+# entries in a window, entries beyond a producer's first loads (384),
 # rows of more than a wave's entries, chains of more than 8 links, the rings of
 # staged entries (4096) and values (8192) wrapping, and windows without entries.
 @pytest.mark.parametrize("n,lengths,d,delay", [
     (6000, [1], 700, 2047), (300, [128], 128, 15), (260, [127, 128, 129, 1], 400, 15),
     (900, [100], 150, 4), (3000, [20, 33, 40], 90, 50), (4000, [0, 0, 0, 3], 5, 1),
-    (3000, [0] * 40 + [200], 300, 7)])
+    (3000, [0] * 40 + [200], 300, 7),
+    (6000, [1], 700, 1535), (300, [128], 140, 11), (300, [128], 140, 12)])
 @pytest.mark.parametrize("loss,with_val", [(0, False), (1, True)])
 def test_window_staging_edges(gpu, n, lengths, d, delay, loss, with_val):
     native = native_mod()
