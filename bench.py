@@ -658,7 +658,9 @@ def main():
     one_cu = mf and L > 0 and n < 16 * L and (g["n_users"] + g["n_items"]) * 256 <= 2 ** 32
     syncfree = mode == 2 or (mode == 0 and L > 0 and (n >= 8 * L or one_cu))
     if batch:
-        kernel = "k_batch_syncfree (mini-batch epoch)" if mode != 1 else \
+        kernel = ("k_batch_syncfree or k_batch_flow (mini-batch epoch; the library picks "
+                  "per call, k_batch_flow where few entries of a batch share a feature)") \
+            if mode != 1 else \
             "k_batch_levels (mini-batch epoch)"
     elif delay >= 0:
         kernel = ("k_stale_window or k_stale_epoch (bounded-delay epoch; the library picks "

@@ -361,7 +361,10 @@ int pdb_batch_schedule(const pdb_csr *csr, int64_t n, int64_t d, int64_t batch,
  *     was written by its previous writer (levels->prev_nz over the union
  *     entries), no barriers.  Chosen when levels->prev_nz is set and ws_bytes
  *     covers pdb_epoch_workspace_bytes(d) (opt->epoch_mode = PDB_EPOCH_LEVELS forces
- *     batch levels).
+ *     batch levels).  Where batches->U_host says that few entries share their
+ *     feature with another of their batch (at most one in 32), batch is 8 to
+ *     256 and most batches hold no example of more than 128 entries, the
+ *     examples of a batch wait one by one, else the batch does.
  * ws: at least pdb_epoch_workspace_bytes(0).  Asynchronous; a device error
  * (watchdog) is reported by pdb_workspace_status on ws. */
 int pdb_batch_epoch(const pdb_csr *csr, const float *labels, int64_t n, int64_t d, int64_t batch,

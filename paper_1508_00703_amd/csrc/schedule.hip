@@ -950,8 +950,8 @@ struct WalkShared {
 
 // From how many runs on a window's rows are pushed: one per kPushRows rows.
 // 64 rows cost about 1.0 us that way, a run 0.6 us: with runs of 24 rows the
-// two take the same.  (10,000 rows of 10 Zipf
-// entries, runs of 9: 825 -> 343 us.)
+// two take the same.  (10,000 rows of 10 Zipf entries, runs of 9: 825 -> 343
+// us.)
 constexpr int kPushRows = 24;
 
 // Levels of the window's rows c0 .. c0 + 63 (one wave), M folded over the
