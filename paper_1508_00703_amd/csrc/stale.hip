@@ -336,8 +336,8 @@ __global__ __launch_bounds__(kBlock) void k_win_from(const int64_t *__restrict__
 // last windows of kWinV entries together, at least three before this one; so
 // no window from k - 3 on wrote it.
 // 200,000 examples of 20-40 entries over 100,000 Zipf-1.1 features, delay 8:
-// 54.0 -> 29 ms (2.4 -> 1.3 us a window of 9); delay 1 42.4 -> 25.7 ms for
-// 50,000, delay 31 8.0 -> 5.8 ms. Before, every wave loaded, staged and waited
+// 54.0 -> 28.8 ms (2.4 -> 1.3 us a window of 9); delay 1 42 -> 22.5 ms for
+// 50,000, delay 31 7.6 -> 5.2 ms. Before, every wave loaded, staged and waited
 // for memory in every window, and a chain followed its entries' links, two
 // dependent LDS reads each.  With the same data flow but the staging done by
 // all the waves, loads two windows ahead, a window took 2.1 us.  What is left
@@ -363,10 +363,12 @@ struct WinShared {
     float sink;
     int2 win[kWinAhead];  // first entry, last + 1
     int staged[kWinProd];  // producer: its windows before this one are staged
-    int done;              // windows the consumers are through with
+    alignas(16) int done;  // windows the consumers are through with
     int freeq;             // their entries end here
     int ackq;              // entries of the windows whose writes are in w
+    int stop;              // a producer gave up: every wave leaves
     unsigned arrived;      // consumer waves at the barriers so far
+    int tripped;           // one producer marks them
 };
 
 struct WinArgs {
@@ -377,6 +379,8 @@ struct WinArgs {
     const int32_t *place, *from;
     int64_t n, nnz, W;
     float lr;
+    Ctrl *ctrl;
+    int64_t timeout;
 };
 
 __device__ __forceinline__ int win_get(const int *p) {
@@ -386,6 +390,48 @@ __device__ __forceinline__ int win_get(const int *p) {
 __device__ __forceinline__ void win_set(int *p, int v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+
+// the words that a producer's wait for room looks at, by one LDS read
+struct WinRoom {
+    int done, freeq, ackq, stop;
+};
+__device__ __forceinline__ WinRoom win_room(const WinShared &S) {
+    __asm__ __volatile__("" ::: "memory");  // read again at every poll
+    const int4 r = *reinterpret_cast<const int4 *>(&S.done);
+    __asm__ __volatile__("" ::: "memory");
+    return WinRoom{__builtin_amdgcn_readfirstlane(r.x), __builtin_amdgcn_readfirstlane(r.y),
+                   __builtin_amdgcn_readfirstlane(r.z), __builtin_amdgcn_readfirstlane(r.w)};
+}
+
+// The watchdog.  Every wait of the block is for a producer, or for consumers
+// that wait for one, and a producer waits only for room, which the consumers
+// make.  So the producers watch for all: in their waits for room, and producer 0
+// until the consumers are through.  The first to give up makes the barriers'
+// count jump far ahead and sets the stop word, which ends the other producers'
+// waits; each marks its `staged` as it leaves.  The consumers' polls are on the
+// chain and look at nothing else: a marked word ends the wait, and the
+// window's last barrier tells by its count whether there is a next window.
+// (A clock and a stop word in the consumers' own polls: 50,000 examples of
+// 20-40 entries, delay 1, 32.5 ms; a test after each of their waits 27.6; this
+// 22.5, where window numbers of 64 bits took 25.5 and no watchdog at all, with
+// 64 bits, 24.2.)
+constexpr unsigned kWinGone = 1u << 30;  // beyond what a barrier's count runs ahead
+struct WinWatch {
+    int polls = 0;
+    int64_t t0 = 0;
+    // after every failed poll of a producer
+    __device__ __forceinline__ void check(const WinArgs &p, WinShared &S) {
+        if (++polls % 16) return;
+        const int64_t now = now_ticks();
+        if (polls == 16) t0 = now;
+        if (now - t0 <= p.timeout) return;
+        record_error(p.ctrl, DERR_WAIT_TIMEOUT);
+        if (lane_id() == 0 && atomicExch(&S.tripped, 1) == 0) {
+            atomicAdd(&S.arrived, kWinGone);
+            win_set(&S.stop, 1);  // LDS runs one wave's operations in order
+        }
+    }
+};
 
 // A barrier of the consumer waves (the producers do not take part), for LDS
 // only, in two halves: the LDS runs each wave's operations in order, so a
@@ -398,11 +444,15 @@ struct WinBarrier {
         if (lane_id() == 0) atomicAdd(&S.arrived, 1u);
         __asm__ __volatile__("" ::: "memory");
     }
-    __device__ __forceinline__ void wait(WinShared &S) {
+    // returns how far the count is past this barrier
+    __device__ __forceinline__ int wait(WinShared &S) {
+        int ahead;
         __asm__ __volatile__("" ::: "memory");
-        while ((int)((unsigned)win_get(reinterpret_cast<const int *>(&S.arrived)) - passed) < 0) {
-        }
+        do {
+            ahead = (int)((unsigned)win_get(reinterpret_cast<const int *>(&S.arrived)) - passed);
+        } while (ahead < 0);
         __asm__ __volatile__("" ::: "memory");
+        return ahead;
     }
 };
 
@@ -455,9 +505,17 @@ __device__ void win_produce(const WinArgs &p, WinShared &S, int id, int64_t nwin
     if (id >= nwin || p.nnz == 0) {
         // no entries: bounds alone
         for (int64_t k = id; k < nwin; k += kWinProd) {
-            while (k >= win_get(&S.done) + kWinAhead ||
-                   astart(k + 1) - astart(win_get(&S.done)) > kWinS)
+            WinWatch watch;
+            for (;;) {
+                const WinRoom r = win_room(S);
+                if (r.stop) {
+                    win_set(&S.staged[id], INT_MAX);
+                    return;
+                }
+                if (k < r.done + kWinAhead && astart(k + 1) - astart(r.done) <= kWinS) break;
+                watch.check(p, S);
                 __builtin_amdgcn_s_sleep(1);
+            }
             if (lane == 0) S.win[k & (kWinAhead - 1)] = make_int2(0, 0);
             for (int64_t a = astart(k) + lane; a < astart(k + 1); a += kWave) {
                 S.rb[a & (kWinS - 1)] = 0;
@@ -491,11 +549,17 @@ __device__ void win_produce(const WinArgs &p, WinShared &S, int id, int64_t nwin
         const int64_t a0 = astart(k), a1 = astart(k + 1);
         // room for its entries, examples and bounds, and nothing to read from
         // w that is not there yet
+        WinWatch watch;
         for (;;) {
-            const int done = win_get(&S.done), freeq = win_get(&S.freeq), ackq = win_get(&S.ackq);
-            if (k < done + kWinAhead && a1 - astart(done) <= kWinS && qe - freeq <= kWinS &&
-                qe - ackq <= kWinV)
+            const WinRoom r = win_room(S);
+            if (r.stop) {
+                win_set(&S.staged[id], INT_MAX);
+                return false;
+            }
+            if (k < r.done + kWinAhead && a1 - astart(r.done) <= kWinS && qe - r.freeq <= kWinS &&
+                qe - r.ackq <= kWinV)
                 break;
+            watch.check(p, S);
             __builtin_amdgcn_s_sleep(1);
         }
         __asm__ __volatile__("" ::: "memory");
@@ -531,11 +595,12 @@ __device__ void win_produce(const WinArgs &p, WinShared &S, int id, int64_t nwin
         if (lane == 0) win_set(&S.staged[id], (int)k + 1);
         qs = s1;
         qe = e1;
+        return true;
     };
     for (int64_t k = id; k < nwin; k += 2 * kWinProd) {
-        stage(k, A, B);
+        if (!stage(k, A, B)) return;
         if (k + kWinProd >= nwin) break;
-        stage(k + kWinProd, B, A);
+        if (!stage(k + kWinProd, B, A)) return;
     }
 }
 
@@ -551,7 +616,7 @@ struct WinTurn {
     float wq[kWinTurn], x[kWinTurn];
 };
 
-__device__ __forceinline__ WinTurn win_turn(const WinArgs &p, WinShared &S, int wave, int64_t k) {
+__device__ __forceinline__ WinTurn win_turn(const WinArgs &p, WinShared &S, int wave, unsigned k) {
     constexpr int mask = (1 << kPlaceShift) - 1;
     const int lane = lane_id();
     WinTurn t;
@@ -562,8 +627,8 @@ __device__ __forceinline__ WinTurn win_turn(const WinArgs &p, WinShared &S, int 
     t.qs = __builtin_amdgcn_readfirstlane(win.x);
     const int qe = __builtin_amdgcn_readfirstlane(win.y);
     t.E = qe - t.qs;
-    const int64_t a0 = k * p.W;
-    const int nex = (int)(min(p.n, a0 + p.W) - a0), j = kWinCons - 1 - wave;
+    const unsigned W = (unsigned)p.W, a0 = k * W;  // below 2^31 + W
+    const int nex = (int)(min((unsigned)p.n, a0 + W) - a0), j = kWinCons - 1 - wave;
     if (j < nex) {
         const int jl = min(j + min(lane, kWinTurn - 1) * kWinCons, nex - 1);
         const int bl = S.rb[(a0 + jl) & (kWinS - 1)];
@@ -585,7 +650,7 @@ __device__ __forceinline__ WinTurn win_turn(const WinArgs &p, WinShared &S, int 
 }
 
 template <int LOSS, bool VAL>
-__device__ void win_consume(const WinArgs &p, WinShared &S, int wave, int64_t nwin) {
+__device__ void win_consume(const WinArgs &p, WinShared &S, int wave, unsigned nwin) {
     constexpr int mask = (1 << kPlaceShift) - 1;
     const int lane = lane_id(), tid = wave * kWave + lane, w0 = wave * kWave;
     const unsigned v_a = (unsigned)(uintptr_t)(const lds_f32 *)S.v;
@@ -600,10 +665,12 @@ __device__ void win_consume(const WinArgs &p, WinShared &S, int wave, int64_t nw
     int qb = 0;  // first entry of the window before
     WinBarrier bar;
     WinTurn T = win_turn(p, S, wave, 0);
-    for (int64_t k = 0; k < nwin; ++k) {
+    if (win_get(&S.stop)) return;  // window 0 was not staged
+    const unsigned W = (unsigned)p.W;
+    for (unsigned k = 0;;) {
         const int qs = T.qs, E = T.E;
-        const int64_t a0 = k * p.W;
-        const int nex = (int)(min(p.n, a0 + p.W) - a0);
+        const unsigned a0 = k * W;
+        const int nex = (int)(min((unsigned)p.n, a0 + W) - a0);
         // steps, a wave per example (the last waves first: the first ones head
         // the chains); dot products in the matched order
         const int j = kWinCons - 1 - wave;
@@ -744,11 +811,12 @@ __device__ void win_consume(const WinArgs &p, WinShared &S, int wave, int64_t nw
         bar.arrive(S);
         qb = qs;
         if (k + 1 < nwin) T = win_turn(p, S, wave, k + 1);
-        bar.wait(S);
+        const unsigned last = bar.wait(S) < kWinCons ? nwin : k + 1;
         if (tid == 0) {
             win_set(&S.freeq, qs + E);
             win_set(&S.done, (int)k + 1);
         }
+        if (++k == last) break;
     }
     // the last window's writes, after those of the one before it
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
@@ -764,16 +832,29 @@ __global__ __launch_bounds__(kWinThreads) void k_stale_window(WinArgs p) {
     __shared__ WinShared S;
     if (threadIdx.x < kWinProd) S.staged[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
-        S.done = S.freeq = S.ackq = 0;
+        S.done = S.freeq = S.ackq = S.stop = S.tripped = 0;
         S.arrived = 0;
     }
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(wave_in_block());
     const int64_t nwin = cdiv_dev(p.n, p.W);
     if (wave < kWinCons)
-        win_consume<LOSS, VAL>(p, S, wave, nwin);
+        win_consume<LOSS, VAL>(p, S, wave, (unsigned)nwin);
     else
         win_produce<VAL>(p, S, wave - kWinCons, nwin);
+    if (wave == kWinCons) {
+        // no window left to stage: until the consumers are through
+        for (int done = -1;;) {
+            WinWatch watch;
+            WinRoom r;
+            while ((r = win_room(S)).done == done && !r.stop) {
+                watch.check(p, S);
+                __builtin_amdgcn_s_sleep(8);
+            }
+            if (r.stop || r.done >= nwin) return;
+            done = r.done;
+        }
+    }
 }
 
 constexpr int kWidePer = kWinCap / kWinThreads;  // entries per thread
@@ -1035,7 +1116,8 @@ int launch_stale(const pdb_csr *csr, const float *labels, int64_t n, float *w, f
                                                                       ws.rd, ws.words, from);
             PDB_LAUNCHED();
         }
-        const WinArgs p{csr->row_ptr, csr->col, csr->val, labels, w, place, from, n, nnz, W, lr};
+        const WinArgs p{csr->row_ptr, csr->col, csr->val, labels, w, place, from, n, nnz, W, lr,
+                        ws.ctrl, timeout};
         k_stale_window<LOSS, VAL><<<1, kWinThreads, 0, s>>>(p);
         PDB_LAUNCHED();
         return PDB_OK;

@@ -177,3 +177,39 @@ def test_window_staging_edges(gpu, n, lengths, d, delay, loss, with_val):
     lv = native.Levels(g["n"], len(g["col"]), gpu)
     native.pdb_schedule(csr, None, g["n"], g["d"], lv)
     check_stale(native, gpu, g, lv, delay, opt=dict(stale_mode=2))
+
+
+# A zero watchdog: windows of many examples keep the producers waiting for room
+# (with entries in the rings, and with none at all), a wait gives up and every
+# wave of the block leaves; the workspace reports it once, and the next epoch on
+# it is the delayed one.
+@pytest.mark.parametrize("length,delay", [(20, 63), (0, 1023)])
+def test_zero_watchdog_windowed(gpu, length, delay):
+    import torch
+
+    native = native_mod()
+    n, d = 20_000, 300
+    rng = np.random.default_rng(delay)
+    rows = [set(rng.integers(0, d, length).tolist()) for _ in range(n)]
+    g = structured_problem(rows, 1, True, 6)
+    lv, _ = gpu_schedule(native, gpu, g["row_ptr"], g["col"], g["d"], 0)
+    csr = native.Csr.from_numpy(g["row_ptr"], g["col"], g["val"], gpu)
+    y = torch.from_numpy(g["y"]).to(gpu)
+    w = torch.zeros(g["d"], dtype=torch.float32, device=gpu)
+    ws = native.workspace(native.pdb_stale_workspace_bytes(csr.nnz), gpu)
+
+    def run(**opt):
+        native.pdb_stale_epoch(csr, y, n, g["d"], w, float(g["lr"]), g["loss"], delay, lv, ws=ws,
+                               opt=dict(stale_mode=native.PDB_STALE_WINDOWED, **opt))
+        torch.cuda.synchronize()
+
+    run(spin_timeout_us=0)
+    assert native.pdb_workspace_status(ws) == native.PDB_ERR_DEVICE
+    assert native.pdb_workspace_status(ws) == native.PDB_OK      # cleared by the read
+    w.zero_()
+    run()
+    assert native.pdb_workspace_status(ws) == native.PDB_OK
+    ref = oracle.stale_epoch(g["row_ptr"], g["col"], g["val"], g["y"],
+                             np.zeros(g["d"], np.float32), g["lr"], g["loss"], oracle.MATCHED,
+                             delay)
+    assert np.array_equal(w.cpu().numpy().view(np.int32), ref.view(np.int32))
