@@ -177,7 +177,8 @@ struct ChainShared {
     float mt_t[kRB + kMirror];  // target: [y > 0] (logistic) or y (least squares)
     int seq[kRB];         // position t staged in the slot, ~t when its example has more
                           // than 64 entries, INT_MIN none
-    int ctl[4];           // [0] consumer no longer needs positions < ctl[0]; [1] stop
+    int ctl[4];           // [0] consumer no longer needs positions < ctl[0]; [1] stop;
+                          // [2] a producer's wait lasted longer than the watchdog
     float ring[kRing];    // new weights of cold features written within kD examples
     float lsink[64];      // LDS write target of lanes without an entry
     float zero[4];        // [0] read by lanes without an entry; [1] marks global sources
@@ -197,6 +198,32 @@ template <int LOSS>
 __device__ __forceinline__ float target_of(float y) {
     return LOSS == PDB_LOGISTIC ? (y > 0.0f ? 1.0f : 0.0f) : y;
 }
+
+// The watchdog.  The consumer waits only for examples that a producer stages,
+// and a producer waits only for room, which the consumer makes: the producers
+// watch in those waits.  One that gives up marks the positions that the consumer may
+// be waiting for as examples of more than 64 entries, again at every check:
+// that ends the consumer's run, and ctl[1] then the producers' waits as
+// always.  The consumer, which is the chain, looks at nothing more for it (one
+// more word at every 16th of its failed polls took 117.5 ms for 116.5, this 0.2%:
+// 1,000,000 examples of 50 Zipf-1.2 entries).
+struct ChainWatch {
+    int polls = 0;
+    int64_t t0 = 0;
+    // after every failed poll of a producer
+    __device__ __forceinline__ void check(ChainShared &S, Ctrl *ctrl, int64_t timeout) {
+        if (++polls % 16) return;
+        const int64_t now = now_ticks();
+        if (polls == 16) t0 = now;
+        if (now - t0 <= timeout) return;
+        record_error(ctrl, DERR_WAIT_TIMEOUT);
+        lds_store(&S.ctl[2], 1);
+        // the consumer waits for positions of [ctl[0], ctl[0] + kRB)
+        const int c = __builtin_amdgcn_readfirstlane(lds_load(&S.ctl[0]));
+        static_assert(kRB == kWave, "a lane per slot");
+        lds_store(&S.seq[lane_id()], ~(c + ((lane_id() - c) & (kRB - 1))));
+    }
+};
 
 // Producer wave pid (0..2): stages examples t of the run (batches of kPB, in
 // turn), never more than kRB ahead of the consumer.  For every entry it finds
@@ -248,7 +275,8 @@ __device__ __forceinline__ BatchMeta batch_meta(const SgdOp<LOSS, VAL> &op, int6
 
 template <int LOSS, bool VAL, bool DENSE>
 __device__ void chain_producer(const SgdOp<LOSS, VAL> &op, int pid, int64_t e_beg, int64_t len,
-                               int64_t r0, int hot, ChainShared &S) {
+                               int64_t r0, int hot, ChainShared &S, Ctrl *ctrl,
+                               int64_t timeout) {
     const int lane = lane_id();
     const unsigned wc_base = lds_addr(&g_wcache[0]);
     const unsigned zero_a = lds_addr(&S.zero[0]);
@@ -261,8 +289,10 @@ __device__ void chain_producer(const SgdOp<LOSS, VAL> &op, int pid, int64_t e_be
     int64_t t0 = (int64_t)pid * kPB;
     BatchMeta nxt = batch_meta<LOSS, VAL, DENSE>(op, t0, e_beg, len, r0);
     for (; t0 < len; t0 += 3 * kPB) {
+        ChainWatch watch;
         while (t0 + kPB - 1 >= (int64_t)lds_load(&S.ctl[0]) + kRB) {
             if (lds_load(&S.ctl[1])) return;
+            watch.check(S, ctrl, timeout);
             __builtin_amdgcn_s_sleep(1);
         }
         if (lds_load(&S.ctl[1])) return;
@@ -633,10 +663,11 @@ __device__ int64_t chain_consumer(const SgdOp<LOSS, VAL> &op, int64_t len, int64
 // sequential order of their examples) with the whole block.  width1: every
 // level of the run has one example, so the examples have increasing indices.
 // idx_r0 >= 0: the run is rows idx_r0, idx_r0 + 1, ... in index order
-// instead (perm is not read).
+// instead (perm is not read).  False (every thread) when a wait gave up.
 template <int LOSS, bool VAL>
-__device__ void chain_run(const SgdOp<LOSS, VAL> &op, int64_t e_beg, int64_t e_end, int hot,
-                          int64_t d, Ctrl *ctrl, bool width1, bool fast, int64_t idx_r0 = -1) {
+__device__ bool chain_run(const SgdOp<LOSS, VAL> &op, int64_t e_beg, int64_t e_end, int hot,
+                          int64_t d, Ctrl *ctrl, int64_t timeout, bool width1, bool fast,
+                          int64_t idx_r0 = -1) {
     __shared__ ChainShared S;
     __shared__ int64_t s_done;
     const int wave = wave_in_block();
@@ -667,11 +698,14 @@ __device__ void chain_run(const SgdOp<LOSS, VAL> &op, int64_t e_beg, int64_t e_e
             }
             if (lane_id() == 0) s_done = done;
         } else if (dense_r0 >= 0) {
-            chain_producer<LOSS, VAL, true>(op, wave - 1, pos, e_end - pos, dense_r0, hot, S);
+            chain_producer<LOSS, VAL, true>(op, wave - 1, pos, e_end - pos, dense_r0, hot, S, ctrl,
+                                            timeout);
         } else {
-            chain_producer<LOSS, VAL, false>(op, wave - 1, pos, e_end - pos, -1, hot, S);
+            chain_producer<LOSS, VAL, false>(op, wave - 1, pos, e_end - pos, -1, hot, S, ctrl,
+                                             timeout);
         }
         __syncthreads();
+        if (S.ctl[2]) return false;  // the same for every thread
         for (int i = threadIdx.x; i < hot; i += kBlock) op.w[i] = g_wcache[i];
         __syncthreads();
         pos += s_done;
@@ -687,6 +721,7 @@ __device__ void chain_run(const SgdOp<LOSS, VAL> &op, int64_t e_beg, int64_t e_e
             ++pos;
         }
     }
+    return true;
 }
 
 // first level >= l whose width exceeds thin_max (L if none); block-uniform
@@ -760,7 +795,7 @@ __global__ __launch_bounds__(kBlock) void k_levels_apply(Op op, const int64_t *l
         // same order -- with no entry matched against a window and no
         // boundary between runs
         if (index_order) {
-            chain_run(op, 0, level_ptr[L], hot, d, ctrl, true, fast, 0);
+            chain_run(op, 0, level_ptr[L], hot, d, ctrl, timeout, true, fast, 0);
             return;
         }
     } else {
@@ -791,7 +826,9 @@ __global__ __launch_bounds__(kBlock) void k_levels_apply(Op op, const int64_t *l
                             // to the next such run or wider level
                             const int64_t l3 = find_run_end(l2, L, level_ptr, 1);
                             if (l3 - l2 >= kChainMin) {
-                                chain_run(op, beg, level_ptr[l3], hot, d, ctrl, true, fast);
+                                if (!chain_run(op, beg, level_ptr[l3], hot, d, ctrl, timeout, true,
+                                               fast))
+                                    return;
                                 l2 = l3;
                                 continue;
                             }
@@ -799,7 +836,9 @@ __global__ __launch_bounds__(kBlock) void k_levels_apply(Op op, const int64_t *l
                             if (chain_width > 1) {
                                 l4 = narrow_run_end(l2, L, level_ptr, chain_width);
                                 if (level_ptr[l4] - beg >= kChainMin) {
-                                    chain_run(op, beg, level_ptr[l4], hot, d, ctrl, false, fast);
+                                    if (!chain_run(op, beg, level_ptr[l4], hot, d, ctrl, timeout,
+                                                   false, fast))
+                                        return;
                                     l2 = l4;
                                     continue;
                                 }

@@ -228,6 +228,43 @@ def test_zero_watchdog_level_barriers(gpu):
     check_sgd(native, gpu, g, lv, opt=dict(epoch_mode=native.PDB_EPOCH_LEVELS))
 
 
+def test_zero_watchdog_pipeline(gpu):
+    """The one-block pipeline (narrow levels) with a zero watchdog: a producer's
+    wait for room gives up, the consumer and the other producers leave, the
+    workspace reports PDB_ERR_DEVICE; the next epoch on it is the sequential
+    one.  Rows of 40 consecutive features of 60, each level one example."""
+    import torch
+
+    native = native_mod()
+    rng = np.random.default_rng(9)
+    rows = [{int(x) for x in s + np.arange(40)} for s in rng.integers(0, 20, 50_000)]
+    row_ptr, col = csr_from_rows(rows)
+    g = dict(row_ptr=row_ptr, col=col, n=len(rows), d=60, loss=0, lr=np.float32(0.01), val=None,
+             y=np.where(rng.random(len(rows)) < 0.5, -1.0, 1.0).astype(np.float32))
+    lv, _ = gpu_schedule(native, gpu, row_ptr, col, g["d"], 0)
+    assert lv.max_width_host == 1
+    csr = native.Csr.from_numpy(row_ptr, col, None, gpu)
+    y = torch.from_numpy(g["y"]).to(gpu)
+    w = torch.zeros(g["d"], dtype=torch.float32, device=gpu)
+    ws = native.workspace(native.pdb_epoch_workspace_bytes(0), gpu)
+    # one run over the rows in index order, with and without wider levels allowed
+    for width in (4, 1):
+        opt = dict(epoch_mode=native.PDB_EPOCH_LEVELS, pipeline_width=width)
+        native.pdb_sgd_epoch(csr, y, g["n"], g["d"], w, float(g["lr"]), g["loss"], lv, ws=ws,
+                             opt=dict(opt, spin_timeout_us=0))
+        torch.cuda.synchronize()
+        assert native.pdb_workspace_status(ws) == native.PDB_ERR_DEVICE
+        w.zero_()
+        native.pdb_sgd_epoch(csr, y, g["n"], g["d"], w, float(g["lr"]), g["loss"], lv, ws=ws,
+                             opt=opt)
+        torch.cuda.synchronize()
+        assert native.pdb_workspace_status(ws) == native.PDB_OK
+        ref = oracle.sgd_epoch(row_ptr, col, None, g["y"], np.zeros(g["d"], np.float32), g["lr"],
+                               g["loss"], oracle.MATCHED)
+        assert np.array_equal(w.cpu().numpy().view(np.int32), ref.view(np.int32))
+        w.zero_()
+
+
 def few_runs_input(n=100_000, run_len=700, seed=700):
     """Chain-like rows in runs of run_len (features 0 and 1 take turns) with
     cold features: auto settles it as few runs over a grid."""
