@@ -456,6 +456,15 @@ struct WinBarrier {
     }
 };
 
+// The ring slot of the window's entry (or place) e.  An entry's index reaches
+// 2^31 - 2, and a chunk or a chain's reads run past the window's end, so the
+// sum is unsigned.
+__host__ __device__ constexpr int win_slot(unsigned qs, int e) {
+    return (int)((qs + (unsigned)e) & (unsigned)(kWinS - 1));
+}
+static_assert(win_slot(INT_MAX - 2u, kWinU * kWave) == ((INT_MAX - 2ll + kWinU * kWave) & (kWinS - 1)),
+              "past the last entry of the largest CSR");
+
 // loads of kWinU chunks of entries from q on (clamped into the arrays)
 template <bool VAL>
 struct WinChunk {
@@ -471,19 +480,19 @@ struct WinChunk {
             x[u] = VAL ? p.val[q] : 1.0f;
         }
     }
-    // entries q0 .. of the window [qs, qe) into LDS
-    __device__ __forceinline__ void put(WinShared &S, const float *wv, int q0, int qs, int qe) {
+    // entries off .. of the window [qs, qs + E) into LDS
+    __device__ __forceinline__ void put(WinShared &S, const float *wv, int off, unsigned qs, int E) {
 #pragma unroll
         for (int u = 0; u < kWinU; ++u) {
-            const int q = q0 + u * kWave + lane_id();
-            if (q0 + u * kWave >= qe) break;
-            if (q < qe) {
-                const int i = q & (kWinS - 1);
+            const int e = off + u * kWave + lane_id();
+            if (off + u * kWave >= E) break;
+            if (e < E) {
+                const int i = win_slot(qs, e);
                 S.col[i] = col[u];
                 S.place[i] = place[u];
                 S.from[i] = from[u];
                 S.wv[i] = wv[u];
-                const int at = (qs + (place[u] & ((1 << kPlaceShift) - 1))) & (kWinS - 1);
+                const int at = win_slot(qs, place[u] & ((1 << kPlaceShift) - 1));
                 S.xp[at] = x[u];
                 if (at < 8) S.xp[kWinS + at] = x[u];
             }
@@ -576,7 +585,7 @@ __device__ void win_produce(const WinArgs &p, WinShared &S, int id, int64_t nwin
             S.rb[(a0 + lane) & (kWinS - 1)] = cur.rb;
             S.y[(a0 + lane) & (kWinS - 1)] = cur.y;
         }
-        cur.c.put(S, wv, (int)qs, (int)qs, (int)qe);
+        cur.c.put(S, wv, 0, (unsigned)qs, (int)(qe - qs));
         // what is more than a wave's first loads
         for (int64_t a = a0 + kWave + lane; a < a1; a += kWave) {
             S.rb[a & (kWinS - 1)] = (int32_t)p.row_ptr[a];
@@ -588,7 +597,7 @@ __device__ void win_produce(const WinArgs &p, WinShared &S, int id, int64_t nwin
             for (int u = 0; u < kWinU; ++u)
                 wv[u] = __hip_atomic_load(&p.w[cur.c.col[u]], __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_WORKGROUP);
-            cur.c.put(S, wv, (int)q, (int)qs, (int)qe);
+            cur.c.put(S, wv, (int)(q - qs), (unsigned)qs, (int)(qe - qs));
         }
         if (lane == 0) S.win[k & (kWinAhead - 1)] = make_int2((int)qs, (int)qe);
         __asm__ __volatile__("" ::: "memory");  // LDS runs one wave's operations in order
@@ -609,7 +618,8 @@ __device__ void win_produce(const WinArgs &p, WinShared &S, int id, int64_t nwin
 // and each lane's entry.
 constexpr int kWinTurn = 1;  // three took as long, also where windows hold 16 to 61 examples
 struct WinTurn {
-    int qs, E;
+    unsigned qs;
+    int E;
     float y;
     int b[kWinTurn], m[kWinTurn];
     int f[kWinTurn], pl[kWinTurn];  // as S.from (the read) and S.place
@@ -626,7 +636,7 @@ __device__ __forceinline__ WinTurn win_turn(const WinArgs &p, WinShared &S, int 
     const int2 win = S.win[k & (kWinAhead - 1)];
     t.qs = __builtin_amdgcn_readfirstlane(win.x);
     const int qe = __builtin_amdgcn_readfirstlane(win.y);
-    t.E = qe - t.qs;
+    t.E = qe - (int)t.qs;
     const unsigned W = (unsigned)p.W, a0 = k * W;  // below 2^31 + W
     const int nex = (int)(min((unsigned)p.n, a0 + W) - a0), j = kWinCons - 1 - wave;
     if (j < nex) {
@@ -643,7 +653,7 @@ __device__ __forceinline__ WinTurn win_turn(const WinArgs &p, WinShared &S, int 
             t.f[i] = S.from[q];
             t.pl[i] = S.place[q] & mask;
             t.wq[i] = S.wv[q];
-            t.x[i] = S.xp[(t.qs + t.pl[i]) & (kWinS - 1)];
+            t.x[i] = S.xp[win_slot(t.qs, t.pl[i])];
         }
     }
     return t;
@@ -668,7 +678,8 @@ __device__ void win_consume(const WinArgs &p, WinShared &S, int wave, unsigned n
     if (win_get(&S.stop)) return;  // window 0 was not staged
     const unsigned W = (unsigned)p.W;
     for (unsigned k = 0;;) {
-        const int qs = T.qs, E = T.E;
+        const unsigned qs = T.qs;
+        const int E = T.E;
         const unsigned a0 = k * W;
         const int nex = (int)(min((unsigned)p.n, a0 + W) - a0);
         // steps, a wave per example (the last waves first: the first ones head
@@ -687,7 +698,7 @@ __device__ void win_consume(const WinArgs &p, WinShared &S, int wave, unsigned n
                     const int q = (T.b[i] + t) & (kWinS - 1);
                     const int f = S.from[q], pl = S.place[q] & mask;
                     const float wq = S.wv[q], vr = S.v[f & (kWinV - 1)];
-                    acc[i] = __builtin_fmaf(f & kInRing ? vr : wq, S.xp[(qs + pl) & (kWinS - 1)],
+                    acc[i] = __builtin_fmaf(f & kInRing ? vr : wq, S.xp[win_slot(qs, pl)],
                                             acc[i]);
                 }
             }
@@ -713,7 +724,7 @@ __device__ void win_consume(const WinArgs &p, WinShared &S, int wave, unsigned n
             const int jl = j0 + lane * kWinCons;  // lane i < 4: example j0 + kWinCons i
             const bool has = lane < 4 && jl < nex;
             const int bl = has ? S.rb[(a0 + jl) & (kWinS - 1)] : 0;
-            const int el = has && jl + 1 < nex ? S.rb[(a0 + jl + 1) & (kWinS - 1)] : qs + E;
+            const int el = has && jl + 1 < nex ? S.rb[(a0 + jl + 1) & (kWinS - 1)] : (int)qs + E;
             const float yl = has ? S.y[(a0 + jl) & (kWinS - 1)] : 0.0f;
             int at[4];
 #pragma unroll
@@ -728,7 +739,7 @@ __device__ void win_consume(const WinArgs &p, WinShared &S, int wave, unsigned n
                         const int q = (b + t) & (kWinS - 1);
                         const int f = S.from[q], pl = S.place[q] & mask;
                         const float wq = S.wv[q];
-                        const float v = S.v[f & (kWinV - 1)], x = S.xp[(qs + pl) & (kWinS - 1)];
+                        const float v = S.v[f & (kWinV - 1)], x = S.xp[win_slot(qs, pl)];
                         acc = __builtin_fmaf(f & kInRing ? v : wq, x, acc);
                         if (t0 == 0) at[i] = pl;
                     }
@@ -767,7 +778,7 @@ __device__ void win_consume(const WinArgs &p, WinShared &S, int wave, unsigned n
             base[u] = 0.0f;
             const int e = tid + u * kWinCons * kWave;
             if (w0 + u * kWinCons * kWave >= E) continue;
-            const int q = (qs + e) & (kWinS - 1);
+            const int q = win_slot(qs, e);
             const int pl = S.place[q], f = S.from[q], c = S.col[q];
             const float wq = S.wv[q];
             const float vr = S.v[f & (kWinV - 1)], vh = S.v[f >> 16 & (kWinV - 1)];
@@ -789,7 +800,7 @@ __device__ void win_consume(const WinArgs &p, WinShared &S, int wave, unsigned n
             float v = base[u];
             for (int i = 0; __ballot(i < len) != 0ull; i += 8) {
                 const int ai = min(a + i, kWinCap);
-                const float *const st = &S.st[ai], *const xp = &S.xp[(qs + ai) & (kWinS - 1)];
+                const float *const st = &S.st[ai], *const xp = &S.xp[win_slot(qs, ai)];
                 float sv[8], xv[8];
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
@@ -802,18 +813,18 @@ __device__ void win_consume(const WinArgs &p, WinShared &S, int wave, unsigned n
                     if (t > 0 && __ballot(on) == 0ull) break;
                     const float nv = __builtin_fmaf(-sv[t], xv[t], v);
                     v = on ? nv : v;
-                    const unsigned to = on ? v_a + ((qs + a + i + t) & (kWinV - 1)) * 4u : sink_a;
+                    const unsigned to = on ? v_a + ((qs + (unsigned)(a + i + t)) & (kWinV - 1)) * 4u : sink_a;
                     *(lds_f32 *)(uintptr_t)to = v;
                 }
             }
             last_v[u] = v;
         }
         bar.arrive(S);
-        qb = qs;
+        qb = (int)qs;
         if (k + 1 < nwin) T = win_turn(p, S, wave, k + 1);
         const unsigned last = bar.wait(S) < kWinCons ? nwin : k + 1;
         if (tid == 0) {
-            win_set(&S.freeq, qs + E);
+            win_set(&S.freeq, (int)qs + E);
             win_set(&S.done, (int)k + 1);
         }
         if (++k == last) break;
