@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kBlock) void k_win_places(const int64_t *__restrict
                                                        int64_t n, int64_t W,
                                                        unsigned long long *__restrict__ chain,
                                                        int32_t *__restrict__ place) {
-    __shared__ int32_t s_len[kWinCap], s_base[kWinCap];
+    __shared__ int32_t s_len[kWinWide], s_base[kWinWide];
     __shared__ int32_t s_next;
     for (int64_t k = blockIdx.x; k < cdiv_dev(n, W); k += gridDim.x) {
         const int64_t q0 = row_ptr[k * W];
@@ -336,8 +336,8 @@ __global__ __launch_bounds__(kBlock) void k_win_from(const int64_t *__restrict__
 // last windows of kWinV entries together, at least three before this one; so
 // no window from k - 3 on wrote it.
 // 200,000 examples of 20-40 entries over 100,000 Zipf-1.1 features, delay 8:
-// 54.0 -> 28.8 ms (2.4 -> 1.3 us a window of 9); delay 1 42 -> 22.5 ms for
-// 50,000, delay 31 7.6 -> 5.2 ms. Before, every wave loaded, staged and waited
+// 54.0 -> 28.5 ms (2.4 -> 1.3 us a window of 9); delay 1 42 -> 21.8 ms for
+// 50,000, delay 31 7.6 -> 5.1 ms. Before, every wave loaded, staged and waited
 // for memory in every window, and a chain followed its entries' links, two
 // dependent LDS reads each.  With the same data flow but the staging done by
 // all the waves, loads two windows ahead, a window took 2.1 us.  What is left
@@ -345,7 +345,8 @@ __global__ __launch_bounds__(kBlock) void k_win_from(const int64_t *__restrict__
 // waits for the stores of a window before, or for several, took the same.
 constexpr int kWinProd = 4;
 constexpr int kWinCons = kWinWaves - kWinProd;
-constexpr int kWinPer = (kWinCap + kWinCons * kWave - 1) / (kWinCons * kWave);  // entries per thread
+// a consumer thread's entries of the widest window that the launcher sends here
+constexpr int kWinPer = (kWinWide + kWinCons * kWave - 1) / (kWinCons * kWave);
 constexpr int kWinS = 2 * kWinCap;  // staged entries, and examples
 constexpr int kWinAhead = 16;       // staged windows
 constexpr int kWinU = 6;            // chunks of 64 entries whose loads a producer holds ahead
@@ -359,7 +360,7 @@ struct WinShared {
     float wv[kWinS];      // by entry: its feature's weight in w
     int32_t rb[kWinS];    // by example: first entry
     float y[kWinS];
-    float st[kWinCap + 8];  // by place: step
+    float st[kWinCap + 8];  // by place (below 2^kPlaceShift): step
     float sink;
     int2 win[kWinAhead];  // first entry, last + 1
     int staged[kWinProd];  // producer: its windows before this one are staged
