@@ -179,6 +179,8 @@ struct ChainShared {
                           // than 64 entries, INT_MIN none
     int ctl[4];           // [0] consumer no longer needs positions < ctl[0]; [1] stop;
                           // [2] a producer's wait lasted longer than the watchdog
+    Ctrl *ctrl;           // for the watchdog
+    int64_t timeout;
     float ring[kRing];    // new weights of cold features written within kD examples
     float lsink[64];      // LDS write target of lanes without an entry
     float zero[4];        // [0] read by lanes without an entry; [1] marks global sources
@@ -205,18 +207,19 @@ __device__ __forceinline__ float target_of(float y) {
 // be waiting for as examples of more than 64 entries, again at every check:
 // that ends the consumer's run, and ctl[1] then the producers' waits as
 // always.  The consumer, which is the chain, looks at nothing more for it (one
-// more word at every 16th of its failed polls took 117.5 ms for 116.5, this 0.2%:
-// 1,000,000 examples of 50 Zipf-1.2 entries).
+// more word at every 16th of its failed polls took 117.5 ms for 116.5:
+// 1,000,000 examples of 50 Zipf-1.2 entries).  What the check reads is in
+// LDS: as arguments of the producers it took 0.3% of the epoch.
 struct ChainWatch {
     int polls = 0;
     int64_t t0 = 0;
     // after every failed poll of a producer
-    __device__ __forceinline__ void check(ChainShared &S, Ctrl *ctrl, int64_t timeout) {
+    __device__ __forceinline__ void check(ChainShared &S) {
         if (++polls % 16) return;
         const int64_t now = now_ticks();
         if (polls == 16) t0 = now;
-        if (now - t0 <= timeout) return;
-        record_error(ctrl, DERR_WAIT_TIMEOUT);
+        if (now - t0 <= S.timeout) return;
+        record_error(S.ctrl, DERR_WAIT_TIMEOUT);
         lds_store(&S.ctl[2], 1);
         // the consumer waits for positions of [ctl[0], ctl[0] + kRB)
         const int c = __builtin_amdgcn_readfirstlane(lds_load(&S.ctl[0]));
@@ -275,8 +278,7 @@ __device__ __forceinline__ BatchMeta batch_meta(const SgdOp<LOSS, VAL> &op, int6
 
 template <int LOSS, bool VAL, bool DENSE>
 __device__ void chain_producer(const SgdOp<LOSS, VAL> &op, int pid, int64_t e_beg, int64_t len,
-                               int64_t r0, int hot, ChainShared &S, Ctrl *ctrl,
-                               int64_t timeout) {
+                               int64_t r0, int hot, ChainShared &S) {
     const int lane = lane_id();
     const unsigned wc_base = lds_addr(&g_wcache[0]);
     const unsigned zero_a = lds_addr(&S.zero[0]);
@@ -292,7 +294,7 @@ __device__ void chain_producer(const SgdOp<LOSS, VAL> &op, int pid, int64_t e_be
         ChainWatch watch;
         while (t0 + kPB - 1 >= (int64_t)lds_load(&S.ctl[0]) + kRB) {
             if (lds_load(&S.ctl[1])) return;
-            watch.check(S, ctrl, timeout);
+            watch.check(S);
             __builtin_amdgcn_s_sleep(1);
         }
         if (lds_load(&S.ctl[1])) return;
@@ -685,6 +687,8 @@ __device__ bool chain_run(const SgdOp<LOSS, VAL> &op, int64_t e_beg, int64_t e_e
         if (threadIdx.x < 4) {
             S.ctl[threadIdx.x] = 0;
             S.zero[threadIdx.x] = 0.0f;
+            S.ctrl = ctrl;
+            S.timeout = timeout;
         }
         __syncthreads();
         if (wave == 0) {
@@ -698,11 +702,9 @@ __device__ bool chain_run(const SgdOp<LOSS, VAL> &op, int64_t e_beg, int64_t e_e
             }
             if (lane_id() == 0) s_done = done;
         } else if (dense_r0 >= 0) {
-            chain_producer<LOSS, VAL, true>(op, wave - 1, pos, e_end - pos, dense_r0, hot, S, ctrl,
-                                            timeout);
+            chain_producer<LOSS, VAL, true>(op, wave - 1, pos, e_end - pos, dense_r0, hot, S);
         } else {
-            chain_producer<LOSS, VAL, false>(op, wave - 1, pos, e_end - pos, -1, hot, S, ctrl,
-                                             timeout);
+            chain_producer<LOSS, VAL, false>(op, wave - 1, pos, e_end - pos, -1, hot, S);
         }
         __syncthreads();
         if (S.ctl[2]) return false;  // the same for every thread
