@@ -671,13 +671,19 @@ __device__ bool fast_batch(const BatchOp<LOSS, VAL> &op, const int32_t *uprev,
     __syncthreads();
     // phase 2 from LDS; the features the next batch waits for are published
     // before the others (one CU issues a batch's thousands of scattered
-    // stores, and the waiting batch needs only a few of them)
+    // stores, and the waiting batch needs only a few of them), before those of
+    // any wave: a wave that is through with its chains would put its others ahead
+    // of what a longer chain still owes.  With the barrier in between, batches of
+    // 100 examples of 80 uniform features over 280,000 take 9.5 us for 15.1, of 30
+    // over 200,000 4.5 for 7.3 (5.2 with every chain before any store), of 30-50
+    // Zipf-1.2 features 3.4 for 4.1.
 #pragma unroll
     for (int h = 0; h < kH; ++h) {
         if (h >= hn) break;
         w[h] = chain_apply<VAL>(w[h], step, Sh.ox, qq[h] & 0xFFFF, qq[h] >> 16);
         if (urgent >> h & 1) word_put(bw, f[h], word_pack(w[h], (int)ub + u0 + kBB * h));
     }
+    __syncthreads();
 #pragma unroll
     for (int h = 0; h < kH; ++h) {
         if (h >= hn) break;
