@@ -361,10 +361,14 @@ int pdb_batch_schedule(const pdb_csr *csr, int64_t n, int64_t d, int64_t batch,
  *     was written by its previous writer (levels->prev_nz over the union
  *     entries), no barriers.  Chosen when levels->prev_nz is set and ws_bytes
  *     covers pdb_epoch_workspace_bytes(d) (opt->epoch_mode = PDB_EPOCH_LEVELS forces
- *     batch levels).  Where batches->U_host says that few entries share their
- *     feature with another of their batch (at most one in 32), batch is 8 to
- *     256 and most batches hold no example of more than 128 entries, the
- *     examples of a batch wait one by one, else the batch does.
+ *     batch levels).  A batch waits as a whole, or its examples one by one,
+ *     whichever is the faster by what the batches hold.  One by one takes
+ *     d <= 2^28, a batch of 8 to 256, at most one entry in 32 that shares its
+ *     feature with another of its batch (batches->U_host), and, looked at on
+ *     the device, at most one batch in four with an example of more than 128
+ *     entries or with more than 16,384 entries in all, few features that four or
+ *     more of a batch's examples share, and of its features some, but not most, that
+ *     the batches just before it write.
  * ws: at least pdb_epoch_workspace_bytes(0).  Asynchronous; a device error
  * (watchdog) is reported by pdb_workspace_status on ws. */
 int pdb_batch_epoch(const pdb_csr *csr, const float *labels, int64_t n, int64_t d, int64_t batch,

@@ -694,17 +694,32 @@ __device__ bool fast_batch(const BatchOp<LOSS, VAL> &op, const int32_t *uprev,
     return true;
 }
 
-// Batches that cannot run example by example (k_batch_flow), counted: a wave
-// per batch.
-__global__ __launch_bounds__(kBlock) void k_batch_whole(const int64_t *__restrict__ row_ptr,
-                                                        int64_t n, int64_t B, int64_t nb,
-                                                        Ctrl *ctrl) {
+// Which of the two executions takes an epoch's batches (by_example), from what
+// the batches hold: nb of them of B examples, `samples` of them looked at for
+// the counts of Ctrl (flow_*); fast: on average they fit fast_batch.
+struct FlowRule {
+    int64_t nb, samples, B;
+    bool fast;
+};
+constexpr int64_t kFlowSamples = 128;
+constexpr int kFlowNear = 8;
+
+// Batches that cannot run example by example (k_batch_flow), counted over all
+// batches, a wave per batch; and the sampled batches' counts, a block per
+// batch, one batch from each of r.samples equal stretches of them (not every
+// k-th: inputs repeat).  Batches beyond kFlowCap are not looked at.
+__global__ __launch_bounds__(kBB) void k_batch_fit(const int64_t *__restrict__ row_ptr, int64_t n,
+                                                   int64_t B, const int64_t *__restrict__ bptr,
+                                                   const int64_t *__restrict__ uptr,
+                                                   const int32_t *__restrict__ uprev, FlowRule r,
+                                                   Ctrl *ctrl) {
     __shared__ int s_count;
+    __shared__ unsigned s_awaited, s_crowded;
     if (threadIdx.x == 0) s_count = 0;
     __syncthreads();
-    const int64_t nw = (int64_t)gridDim.x * (kBlock / kWave);
+    const int64_t nw = (int64_t)gridDim.x * kBWaves;
     int count = 0;
-    for (int64_t b = (blockIdx.x * (int64_t)kBlock + threadIdx.x) / kWave; b < nb; b += nw) {
+    for (int64_t b = (blockIdx.x * (int64_t)kBB + threadIdx.x) / kWave; b < r.nb; b += nw) {
         const int64_t i0 = b * B, i1 = min(i0 + B, n);
         bool over = row_ptr[i1] - row_ptr[i0] > kFlowCap;
         for (int64_t i = i0 + lane_id(); i < i1; i += kWave)
@@ -712,27 +727,94 @@ __global__ __launch_bounds__(kBlock) void k_batch_whole(const int64_t *__restric
         count += __ballot(over) != 0;
     }
     if (lane_id() == 0 && count) atomicAdd(&s_count, count);
+    for (int64_t s = blockIdx.x; s < r.samples; s += gridDim.x) {
+        if (threadIdx.x == 0) s_awaited = s_crowded = 0;
+        __syncthreads();
+        const int64_t lo = s * r.nb / r.samples, hi = (s + 1) * r.nb / r.samples;
+        const int64_t b = lo + (int64_t)((unsigned)s * 2654435761u >> 8) % (hi - lo);
+        const int64_t ub = bptr[b], ue = bptr[b + 1], near = bptr[max(b - kFlowNear, (int64_t)0)];
+        unsigned awaited = 0, crowded = 0;  // sums below kFlowCap and B kFlowCap
+        if (uptr[ue] - uptr[ub] <= kFlowCap) {
+            for (int64_t u = ub + threadIdx.x; u < ue; u += kBB) {
+                const int64_t pv = uprev[u];
+                const unsigned c = (unsigned)(uptr[u + 1] - uptr[u]);
+                awaited += pv >= near;  // -1: none
+                crowded += c >= 4 ? c * c : 0;
+            }
+            awaited = wave_sum_u32(awaited);
+            crowded = wave_sum_u32(crowded);
+            if (lane_id() == 0) {
+                atomicAdd(&s_awaited, awaited);
+                atomicAdd(&s_crowded, crowded);
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x == 0 && uptr[ue] - uptr[ub] <= kFlowCap) {
+            atomicAdd(&ctrl->flow_unions, (unsigned long long)(ue - ub));
+            atomicAdd(&ctrl->flow_awaited, (unsigned long long)s_awaited);
+            atomicAdd(&ctrl->flow_crowded, (unsigned long long)s_crowded);
+        }
+    }
     __syncthreads();
     if (threadIdx.x == 0 && s_count) atomicAdd(&ctrl->whole_batches, s_count);
 }
 
-// At most one batch in four does not fit k_batch_flow, which runs such a
-// batch as a whole too, but without fast_batch, whose registers would cost
-// every batch (8.9 -> 11.0 ms for 5,000 batches of 100): 100,000 examples of
-// 100-180 uniform features, batches of 50, none of which fits, take 22.9 ms in
-// k_batch_syncfree and 47.9 ms there.  With 19% of the batches too long
-// (200,000 examples of about 100 features, batches of 64) it is 36.0 and 17.6 ms.
-__device__ __forceinline__ bool by_example(const Ctrl *ctrl, int64_t nb) {
-    return 4 * (int64_t)ctrl->whole_batches <= nb;
+// Example by example (k_batch_flow), where all of this holds; measured on both
+// executions over some 500 inputs: uniform features, permuted ones, Zipf 0.3-1.0
+// and features that a share of the examples has, 3 to 80 entries, batches of 8
+// to 256 (us a batch, as a whole | by example):
+//  * At most one batch in four does not fit.  k_batch_flow runs such a batch as a
+//    whole too, but without fast_batch, whose registers would cost every batch
+//    (8.9 -> 11.0 ms for 5,000 batches of 100).  100-180 uniform features,
+//    batches of 50, none of which fits: 11.4 | 24; about 100 features, batches of
+//    64, 19% of them too long: 11.5 | 5.6.
+//  * Few words are awaited (union entries that one of the kFlowNear batches before
+//    wrote): as a whole, a batch waits once for all of them, by example each is
+//    polled by itself.  What it costs goes with the words per example, what
+//    it gains with the share of the entries that need no wait.  Batches of 100 x 80
+//    uniform features: 12.5 words, 0.16 of the entries, 10.1 | 7.3; 20 and 0.25 9.1 |
+//    10.3; the same 8,000 features in every batch 5.0 | 33.  50 x 80: 12.6 and 0.16
+//    5.3 | 4.7, 20 and 0.25 4.9 | 6.5.  32 x 80: 12.6 and 0.16 3.6 | 3.4; 32 x 30:
+//    9 and 0.30 1.6 | 2.1.  16 x 80: 6.8 and 0.08 2.1 | 1.7, 12.5 and 0.16 2.1 | 2.5.
+//    100 x 3: 1.1 and 0.38 2.5 | 0.67.  Batches beyond fast_batch take longer
+//    as a whole: 200 x 30 11 and 0.38 20 | 7.1, 128 x 80 30 and 0.38 46 | 16, 200 x
+//    40 36 and 0.90 29 | 17 (consecutive features 20 | 21.6), all 27.6 | 28.8.
+//    Beyond 208 examples a batch takes two turns: 256 x 3 0.3 and 0.08 11.7 | 10.5,
+//    0.8 and 0.25 12.1 | 13.2.
+//  * At least two a batch are awaited, else little waits and what counts is the
+//    staging: 32 x 10 of 40 million features 0.31 | 0.48, 8 x 3 0.6 words 0.17 |
+//    0.30, 2 words 0.39 | 0.32; 100 x 10 2.5 words 1.2 | 0.54.
+//  * No crowded features (of fast_batch's batches), which four or more of a
+//    batch's examples share: those all wait for one word and the last of them
+//    applies its list alone.  Squares of their counts per union entry: one
+//    feature in every example beside 80 rare ones, batches of 50 0.6 5.4 | 12.0,
+//    of 100 1.2 11.1 | 24.8, of 16 0.2 1.7 | 4.0; in half of them, batches of 32
+//    0.1 3.3 | 4.1; 80 Zipf-0.7 features of 20 million, batches of 32 0.017
+//    2.4 | 3.9, of 16 0.004 1.65 | 2.2; one in a tenth of the examples, batches of
+//    100 0.014 10.7 | 3.6, of 32 0.004 3.2 | 1.8, of 16 0.0009 1.6 | 1.25.
+__device__ __forceinline__ bool by_example(const Ctrl *ctrl, FlowRule r) {
+    const unsigned long long unions = ctrl->flow_unions, awaited = ctrl->flow_awaited;
+    const unsigned long long samples = r.samples, examples = samples * r.B;
+    if (4 * (int64_t)ctrl->whole_batches > r.nb || awaited < 2 * samples) return false;
+    if (!r.fast)
+        return r.B > 2 * kFlowWorkers * kFlowG ? 8 * awaited <= unions
+                                               : awaited <= 30 * examples &&
+                                                     10 * awaited <= 9 * unions;
+    const bool few = r.B < 32;  // at most two or three examples a worker
+    if ((few ? 512 : r.B < 64 ? 128 : 64) * ctrl->flow_crowded > unions) return false;
+    return (awaited <= 4 * examples && 2 * awaited <= unions) ||
+           (few ? awaited <= 7 * examples && 10 * awaited <= unions
+                : awaited <= 13 * examples && 5 * awaited <= unions);
 }
 
 template <int LOSS, bool VAL>
 __global__ __launch_bounds__(kBB) void k_batch_syncfree(BatchOp<LOSS, VAL> op,
                                                        const int32_t *__restrict__ uprev,
                                                        unsigned long long *bw, int64_t nb,
-                                                       bool flow, Ctrl *ctrl, int64_t timeout) {
+                                                       bool flow, FlowRule rule, Ctrl *ctrl,
+                                                       int64_t timeout) {
     __shared__ SfShared Sh;
-    if (flow && by_example(ctrl, nb)) return;
+    if (flow && by_example(ctrl, rule)) return;
     for (;;) {
         if (threadIdx.x == 0) {
             Sh.ticket = (int64_t)atomicAdd(&ctrl->ticket, 1ull);
@@ -1143,15 +1225,15 @@ __device__ bool flow_group(const BatchOp<LOSS, VAL> &op, unsigned long long *bw,
 template <int LOSS, bool VAL, int G>
 __global__ __launch_bounds__(kBB) void k_batch_flow(BatchOp<LOSS, VAL> op,
                                                    const int32_t *__restrict__ uprev,
-                                                   unsigned long long *bw, int64_t nb, Ctrl *ctrl,
-                                                   int64_t timeout) {
+                                                   unsigned long long *bw, int64_t nb,
+                                                   FlowRule rule, Ctrl *ctrl, int64_t timeout) {
     __shared__ union {
         SfShared g;
         FlowShared f;
     } Sh;
     __shared__ int64_t s_ticket;
     __shared__ int s_long;
-    if (!by_example(ctrl, nb)) return;
+    if (!by_example(ctrl, rule)) return;
     for (;;) {
         if (threadIdx.x == 0) {
             s_ticket = (int64_t)atomicAdd(&ctrl->ticket, 1ull);
@@ -1247,34 +1329,36 @@ int launch_batch_syncfree(const BatchOp<LOSS, VAL> &op, const pdb_levels *lv, in
     // that slow the frontier's memory accesses
     const int64_t cap = opt.batch_sf_blocks;
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(cus, cap), nb));
-    // Example by example where few entries share their feature with another of
-    // the batch, else a batch at a time.  The line: at 3.6% of the entries the
-    // two take about the same (16.7 ms a batch at a time, 15.7 ms by example,
-    // 200,000 examples of 30 uniform features over 20,000, batches of 50), at
-    // 1.4% 16.8 and 8.2 ms, at 5.8% 20.9 and 26.9 ms, at 58% (Zipf 1.2) 25 and
-    // 87 ms.  A block takes one batch, so batches of fewer examples than about
-    // half a block's waves leave it idle (50,000 examples of 80 features over
-    // 2 million, a batch at a time and by example: batches of 4 3.1 and 3.8 ms,
-    // of 8 4.4 and 2.3 ms).  It addresses words with 32-bit byte offsets.
+    // Example by example where by_example says so, else a batch at a time.  Asked
+    // only where few entries share their feature with another of the batch (at
+    // 3.6% of them 200,000 examples of 30 uniform features over 20,000, batches of
+    // 50, took 16.7 ms a batch at a time and 15.7 by example, at 5.8% 20.9 and
+    // 26.9, at 58%, Zipf 1.2, 25 and 87).  A block takes one batch, so batches of
+    // fewer examples than about half a block's waves leave it idle (50,000
+    // examples of 80 features over 2 million: batches of 4 3.1 and 3.8 ms, of 8
+    // 4.4 and 2.3 ms).  It addresses words with 32-bit byte offsets.
     const bool flow = U > 0 && 32 * (nnz - U) <= nnz && op.B >= 8 && op.B <= kFlowB &&
                       d <= int64_t(1) << 28;
+    const bool fast = op.B <= (int64_t)kBWaves * kG && nnz <= kCap * nb;  // fast_batch, on average
+    const FlowRule rule{nb, std::min(nb, kFlowSamples), op.B, fast};
     if (flow) {
         // what a batch holds is on the device: both kernels are launched, and
         // one of them returns at once (5 us)
-        k_batch_whole<<<grid_for(nb, kBlock / kWave, 1024), kBlock, 0, s>>>(op.row_ptr, op.n, op.B,
-                                                                           nb, ctrl);
+        k_batch_fit<<<grid_for(std::max(rule.samples, cdiv(nb, kBWaves)), 1, 512), kBB, 0, s>>>(
+            op.row_ptr, op.n, op.B, op.bptr, op.uptr, lv->prev_nz, rule, ctrl);
         PDB_LAUNCHED();
         // the most examples per worker that a batch needs, so that they are all in
         // flight together: with half as many, batches of 128 took 50 ms, not 15.7
         if (op.B <= kFlowWorkers * kFlowG)
-            k_batch_flow<LOSS, VAL, kFlowG><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, ctrl,
-                                                                 timeout);
+            k_batch_flow<LOSS, VAL, kFlowG><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, rule,
+                                                                 ctrl, timeout);
         else
             k_batch_flow<LOSS, VAL, 2 * kFlowG><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb,
-                                                                     ctrl, timeout);
+                                                                     rule, ctrl, timeout);
         PDB_LAUNCHED();
     }
-    k_batch_syncfree<LOSS, VAL><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, flow, ctrl, timeout);
+    k_batch_syncfree<LOSS, VAL><<<grid, kBB, 0, s>>>(op, lv->prev_nz, bw, nb, flow, rule, ctrl,
+                                                       timeout);
     PDB_LAUNCHED();
     if (d > 0) {
         k_bw_out<<<grid_for(d, kBlock, 8192), kBlock, 0, s>>>(bw, op.w, d);

@@ -74,7 +74,11 @@ struct Ctrl {
     unsigned pipe_xmax;  // bits of max |x|
     int pipe_bad;        // some w0 is not finite or is -0, or some x is not finite
     int pipe_fast;       // the select-free step is exact for this epoch
-    int pad[34];
+    // sync-free mini-batches, of the sampled batches: union entries, those whose
+    // previous one is in one of the kFlowNear batches before, and entries of
+    // crowded features (squares of their counts)
+    unsigned long long flow_unions, flow_awaited, flow_crowded;
+    int pad[28];
     float sink[64];  // target of stores from lanes with nothing to store
 };
 static_assert(sizeof(Ctrl) == 512, "Ctrl is two 256-byte lines");

@@ -216,6 +216,37 @@ def test_full_size_batch_levels(gpu, cfg):
     check_batch_epoch(native, gpu, g, 100, bt, lv, opt=dict(epoch_mode=1))
 
 
+def by_example(g, B, bt, lv):
+    """The library's rule for running batches example by example, from all batches
+    (which is what it looks at, when there are at most 128)."""
+    nnz, U, nb = len(g["col"]), bt.U_host, bt.nb
+    lengths = np.diff(g["row_ptr"])
+    first = np.arange(0, g["n"], B)
+    if 32 * (nnz - U) > nnz or not 8 <= B <= 256:
+        return False
+    whole = (np.maximum.reduceat(lengths, first) > 128) | (np.add.reduceat(lengths, first) > 16384)
+    bptr, uptr = bt.bptr.cpu().numpy(), bt.uptr.cpu().numpy()[:U + 1]
+    near = np.repeat(bptr[np.maximum(np.arange(nb) - 8, 0)], np.diff(bptr))
+    seen = np.repeat(np.diff(uptr[bptr]) <= 16384, np.diff(bptr))
+    count = np.diff(uptr)[seen]
+    awaited = (lv.prev_nz.cpu().numpy()[:U] >= near)[seen].sum()
+    samples, unions = min(nb, 128), seen.sum()
+    awaited, examples = awaited * samples / nb, samples * B
+    unions = unions * samples / nb
+    if 4 * whole.sum() > nb or awaited < 2 * samples:
+        return False
+    if B > 128 or nnz > 8192 * nb:
+        if B > 208:
+            return bool(8 * awaited <= unions)
+        return bool(awaited <= 30 * examples and 10 * awaited <= 9 * unions)
+    crowded = (count[count >= 4] ** 2).sum() * samples / nb
+    if (512 if B < 32 else 128 if B < 64 else 64) * crowded > unions:
+        return False
+    far, share = (7, 10) if B < 32 else (13, 5)
+    return bool((awaited <= 4 * examples and 2 * awaited <= unions) or
+                (awaited <= far * examples and share * awaited <= unions))
+
+
 # Batches whose features mostly have one entry each (at most one entry in 32
 # shares its feature with another of its batch) run example by example.  Edges:
 # examples per worker and per block (104, 208, 256), entries per example (0,
@@ -243,11 +274,70 @@ def test_batches_example_by_example(gpu, B, extra, loss, with_val):
     if extra == "long":
         rows[350] = set(sample(range(d), 129))
     if extra == "shared":
-        n = 3000  # few shared features overall, 4500 entries on 45 of them in one batch
+        n = 3000  # few shared features overall, in one batch 4500 entries on 1500 of them
         rows += [set(sample(range(d), 100)) for _ in range(1200)]
         for i in range(700, 800):
-            rows[i] = set(range(45))
+            rows[i] = {(45 * (i - 700) + k) % 1500 for k in range(45)}
     g = structured_problem(rows, loss, with_val, 5 + B, B)
     bt, lv = check_batch_schedule(native, gpu, g["row_ptr"], g["col"], g["d"], B)
-    assert 32 * (len(g["col"]) - bt.U_host) <= len(g["col"])
+    assert by_example(g, B, bt, lv) == (extra != "all long")
     check_batch_epoch(native, gpu, g, B, bt, lv)
+
+
+def distinct_draws(n, m, d, seed):
+    rng = np.random.default_rng(seed)
+    return [set(rng.integers(0, d, m).tolist()) for _ in range(n)]
+
+
+# Inputs on both sides of the rule's lines, few shared entries all of them: the
+# words awaited (union entries that one of the 8 batches before wrote) per example and as
+# a share, a feature in every example or in some, hardly any word awaited.
+@pytest.mark.parametrize("B,m,d,hot,want", [
+    (100, 80, 400_000, 0, True), (100, 80, 340_000, 0, True), (100, 80, 220_000, 0, False),
+    (64, 30, 66_000, 0, True), (64, 30, 50_000, 0, False), (100, 10, 18_000, 0, True),
+    (16, 40, 50_000, 0, True), (16, 60, 60_000, 0, False), (16, 10, 3_000, 0, True),
+    (200, 40, 130_000, 0, True), (128, 80, 180_000, 0, True), (210, 20, 280_000, 0, True),
+    (210, 20, 180_000, 0, False), (50, 80, 400_000, 1, False), (200, 60, 900_000, 1, True),
+    (32, 10, 10_000_000, 0, False)])
+def test_which_batches_run_by_example(gpu, B, m, d, hot, want):
+    native = native_mod()
+    rows = distinct_draws(60 * B, m, d, B + d)
+    rows = [{0} | {f + 1 for f in r} for r in rows] if hot else rows
+    g = structured_problem(rows, 1, True, B, B)
+    bt, lv = check_batch_schedule(native, gpu, g["row_ptr"], g["col"], g["d"], B)
+    assert 32 * (len(g["col"]) - bt.U_host) <= len(g["col"])
+    assert by_example(g, B, bt, lv) == want
+    check_batch_epoch(native, gpu, g, B, bt, lv)
+
+
+# More words awaited than the block's list holds (3072): every block's first
+# batch waits for most of its words, those before it not having begun.  Then the
+# same under a zero watchdog: the waits give up, every block leaves, the workspace
+# reports it once, and the next epoch on it is the sequential one.
+@pytest.mark.parametrize("B,d", [(100, 380_000), (200, 400_000)])
+def test_by_example_many_awaited_and_zero_watchdog(gpu, B, d):
+    import torch
+
+    native = native_mod()
+    g = structured_problem(distinct_draws(40 * B, 80, d, B), 1, True, B, B)
+    bt, lv = check_batch_schedule(native, gpu, g["row_ptr"], g["col"], g["d"], B)
+    assert by_example(g, B, bt, lv)
+    pn, bptr = lv.prev_nz.cpu().numpy()[:bt.U_host], bt.bptr.cpu().numpy()
+    assert (pn[bptr[25]:bptr[26]] >= 0).sum() > 3072  # of the 26th of 32 batches in flight
+    check_batch_epoch(native, gpu, g, B, bt, lv)
+    csr = native.Csr.from_numpy(g["row_ptr"], g["col"], g["val"], gpu)
+    y = torch.from_numpy(g["y"]).to(gpu)
+    w = torch.zeros(g["d"], dtype=torch.float32, device=gpu)
+    ws = native.workspace(native.pdb_epoch_workspace_bytes(g["d"]), gpu)
+    native.pdb_batch_epoch(csr, y, g["n"], g["d"], w, float(g["lr"]), g["loss"], bt, lv, ws=ws,
+                           opt=dict(spin_timeout_us=0))
+    torch.cuda.synchronize()
+    assert native.pdb_workspace_status(ws) == native.PDB_ERR_DEVICE
+    assert native.pdb_workspace_status(ws) == native.PDB_OK      # cleared by the read
+    w.zero_()
+    native.pdb_batch_epoch(csr, y, g["n"], g["d"], w, float(g["lr"]), g["loss"], bt, lv, ws=ws)
+    torch.cuda.synchronize()
+    assert native.pdb_workspace_status(ws) == native.PDB_OK
+    ref = oracle.batch_epoch(g["row_ptr"], g["col"], g["val"], g["y"],
+                             np.zeros(g["d"], np.float32), g["lr"], g["loss"], oracle.MATCHED, B)
+    assert np.array_equal(w.cpu().numpy().view(np.int32), ref.view(np.int32))
