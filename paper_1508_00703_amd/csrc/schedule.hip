@@ -1851,6 +1851,15 @@ int build_col_ptr(const uint32_t *sk, int64_t nnz, int64_t d, int64_t *col_ptr, 
     return PDB_OK;
 }
 
+// K1: the entries sorted by feature, in one of the radix buffer pairs
+int build_sorted(const pdb_csr *csr, int64_t d, const SchedWs &w, uint32_t **sk, uint32_t **sv,
+                 hipStream_t s) {
+    const int bits = bit_length(d > 1 ? (uint64_t)(d - 1) : 1);
+    PDB_HIP(radix_sort_pairs(reinterpret_cast<const uint32_t *>(csr->col), nullptr, csr->nnz, bits,
+                             w.kA, w.vA, w.kB, w.vB, w.hist, w.scan_tmp, sk, sv, s));
+    return PDB_OK;
+}
+
 // K1 + K2 into the workspace: previous-writer entries into pn; the entries
 // sorted by feature in (*skeys_out, *svals_out).  The rows of the entries and
 // the features' positions are for the callers that need them (build_rows,
@@ -1859,9 +1868,8 @@ int build_conflicts(const pdb_csr *csr, int64_t d, SchedWs &w, int32_t *pn,
                     const uint32_t **skeys_out, const uint32_t **svals_out, hipStream_t s) {
     const int64_t nnz = csr->nnz;
     uint32_t *sk = nullptr, *sv = nullptr;
-    const int bits = bit_length(d > 1 ? (uint64_t)(d - 1) : 1);
-    PDB_HIP(radix_sort_pairs(reinterpret_cast<const uint32_t *>(csr->col), nullptr, nnz, bits,
-                             w.kA, w.vA, w.kB, w.vB, w.hist, w.scan_tmp, &sk, &sv, s));
+    const int rc = build_sorted(csr, d, w, &sk, &sv, s);
+    if (rc != PDB_OK) return rc;
     if (nnz > 0) {
         // the sort's buffers: the candidates array and pn, and the radix pair
         // not holding the sorted entries
@@ -1949,9 +1957,9 @@ extern "C" int pdb_transpose(const pdb_csr *csr, int64_t n, int64_t d, int64_t *
     int rc = sched_common_checks(csr, n, d, ws, ws_bytes, &w);
     if (rc != PDB_OK) return rc;
     if (!col_ptr || (csr->nnz > 0 && !csc_row)) return PDB_ERR_INVALID_ARG;
-    const uint32_t *sk, *sv;
+    uint32_t *sk, *sv;
     rc = build_rows(csr, n, w, stream);
-    if (rc == PDB_OK) rc = build_conflicts(csr, d, w, w.pn, &sk, &sv, stream);
+    if (rc == PDB_OK) rc = build_sorted(csr, d, w, &sk, &sv, stream);
     if (rc == PDB_OK) rc = build_col_ptr(sk, csr->nnz, d, col_ptr, stream);
     if (rc != PDB_OK) return rc;
     if (csr->nnz > 0) {
