@@ -1221,7 +1221,9 @@ __device__ bool flow_group(const BatchOp<LOSS, VAL> &op, unsigned long long *bw,
 // complete in order, so a wave that both published and polled would see its
 // next words only after its stores were acknowledged (10.3 ms with sixteen
 // waves that each did both).  A worker reads its examples' words once, then
-// touches only LDS and its registers until it publishes.
+// touches only LDS and its registers until it publishes.  Sixteen waves leave a
+// lane 128 registers; of what the roles hold 35 to 47 go to scratch with G = 8,
+// 83 to 119 with 16 (fast_batch: 0 to 2, with stored values 17 to 21).
 template <int LOSS, bool VAL, int G>
 __global__ __launch_bounds__(kBB) void k_batch_flow(BatchOp<LOSS, VAL> op,
                                                    const int32_t *__restrict__ uprev,

@@ -38,9 +38,8 @@ __device__ __forceinline__ void word_put_wg(unsigned long long *base, int64_t i,
 }
 
 // Sleeps about 2^min(round, 3) x 64 cycles (s_sleep takes a constant):
-// for waits where many words of many blocks are polled at once (mini-batch
-// unions, dense partial sums), so that waiting waves do not crowd the
-// frontier's accesses.
+// for waits where many words of many blocks are polled at once (dense
+// partial sums), so that waiting waves do not crowd the frontier's accesses.
 __device__ __forceinline__ void word_backoff(int round) {
     switch (round < 3 ? round : 3) {
         case 0: __builtin_amdgcn_s_sleep(1); break;
@@ -50,11 +49,11 @@ __device__ __forceinline__ void word_backoff(int round) {
     }
 }
 
-// Sleeps 64 cycles, then 128 from the second round on: for the per-example
-// waits of the sync-free epochs, where a longer back-off only delays the wave
-// that is next on the chain (capped at 512 cycles it cost the config-4 epoch
-// 12%: 38.9 ms against 34.7 ms; the mini-batch epoch's union waits instead
-// lost 30% with this one).
+// Sleeps 64 cycles, then 128 from the second round on: for the waits of the
+// sync-free epochs, where a longer back-off only delays the wave that is next
+// on the chain (capped at 512 cycles it cost the config-4 epoch 12%: 38.9 ms
+// against 34.7 ms, and a mini-batch's wait for its union 0 to 5%, batches of 32
+// to 128 examples).
 __device__ __forceinline__ void word_backoff_short(int round) {
     if (round == 0) __builtin_amdgcn_s_sleep(1);
     else __builtin_amdgcn_s_sleep(2);
